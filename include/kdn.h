@@ -256,7 +256,7 @@ size_t kdn_gain_workspace_bytes(int32_t variant, int32_t N, int32_t B, int32_t T
  * "Detailed Experimental Setup"); this is the reverse mode of the same recurrences
  * (Prop. "Diagonal Kalman Delta Network", Prop. "Isotropic Kalman Delta Network"), taken
  * through the chunked memory scan (App. "Hardware-Efficient Chunkwise Algorithm", Sec.
- * "Chunkwise Memory Scan") with decay ratios formed from cumulative log-decays, and through the
+ * "Chunkwise Memory Scan") with decay ratios formed as products of the gates, and through the
  * variance recurrence as a reverse linear recurrence of its adjoint.
  *   Inputs: those of the forward (same layouts, dtype, packing, S0 / P0 NULL = 0 / 1, mu,
  *   scale; alpha_per_channel as in kdn_forward_iso, ignored for variant 0), and
@@ -268,12 +268,12 @@ size_t kdn_gain_workspace_bytes(int32_t variant, int32_t N, int32_t B, int32_t T
  *   the call (KDN_ERR_INVALID_ARG). Tokens of a packed batch outside every sequence are not
  *   written.
  *   workspace: at least kdn_backward_workspace_bytes(...) bytes (KDN_ERR_WORKSPACE), about
- *   8 KB per token and head at dk = dv = 128; no initialisation needed.
- * Seven kernels run on `stream`: the forward's chunk summaries and carry scan, then a per-chunk
+ *   6.5 KB per token and head at dk = dv = 128; no initialisation needed.
+ * Eight kernels run on `stream`: the forward's chunk summaries and carry scan, then a per-chunk
  * replay of the gains and the chunk matrices, a forward walk that checkpoints the state at every
  * chunk start, a reverse walk that carries the state's adjoint, the per-chunk gradients, the
  * reverse scan of the variance adjoint and the per-token gradients of the gains. The arithmetic
- * is float32 throughout, with the cumulative log-decays in float64. Decay ratios between
+ * is float32 throughout. Decay ratios between
  * 16-token blocks are products of factors at most one; inside a block they are referenced to
  * its token 8, exact while the product of alpha over any 8 consecutive tokens of an aligned
  * 16-token block stays above 2^-100 per channel (every alpha >= 2^-12.5 ~ 1.7e-4 suffices).

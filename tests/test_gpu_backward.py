@@ -107,6 +107,38 @@ def test_backward_packed_ragged(variant):
     compare_backward(x, seed=95)
 
 
+@pytest.mark.parametrize("dk,dv", [(16, 16), (64, 16), (128, 32)])
+@pytest.mark.parametrize("T", [1, 16, 65, 127])
+@pytest.mark.parametrize("variant,apc", [("diag", True), ("iso", False)])
+def test_backward_tile_edges(variant, apc, T, dk, dv):
+    """Chunks of one token, of whole 16-token blocks, one past and one short of a chunk; heads with
+    fewer key tiles than waves, one value tile of 16, and key and value widths that differ. float32
+    sums of at most 128 terms: the bound of the other float32 cases."""
+    x = W.draw_inputs(variant, "f32", 2, T, 2, dk, dv, seed=97, alpha_per_channel=apc,
+                      random_state=True)
+    compare_backward(x, seed=97)
+
+
+@pytest.mark.parametrize("variant", ["diag", "iso"])
+def test_backward_state_adjoints_only(variant):
+    """No dO: the gradients of the final states alone."""
+    from paper_2609_07816_amd import kdn
+    x = W.draw_inputs(variant, "bf16", 1, 100, 2, 64, 32, seed=98, random_state=True)
+    _, dS, dP = adjoints(x, 98)
+    d = to_device(x)
+    got = kdn.backward(x.variant, d["q"], d["k"], d["v"], d["alpha"], d["omega"], d["r"],
+                       S0=d["S0"], P0=d["P0"], mu=x.mu, scale=x.scale,
+                       dS_T=torch.from_numpy(dS).cuda(), dP_T=torch.from_numpy(dP).cuda())
+    torch.cuda.synchronize()
+    ref = oracle.backward(x.variant, *[x.f64(n) for n in NAMES], S0=x.S0, P0=x.P0, mu=x.mu,
+                          scale=x.scale, dO=np.zeros((x.B, x.T, x.H, x.dv)), dS_T=dS, dP_T=dP)
+    for name in GRADS:
+        if name == "dq":  # q reaches the loss through o only
+            assert not np.any(host_f64(got[name]))
+        else:
+            check(name, host_f64(got[name]), ref[name])
+
+
 def test_backward_small_gates_and_zero_noise():
     """Gates down to 0.01 (decays far below the float32 range over a chunk), omega = 0 and a
     tiny r: every decay ratio stays at most one."""
