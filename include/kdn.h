@@ -137,7 +137,7 @@ kdn_status_t kdn_forward_iso(const void* q, const void* k, const void* v, const 
  *   packed only: the chunk-offset table (4 (N + 1)) and the walk order (4 N);
  *   the chunk summaries (16 M H c) and the carries into every chunk (8 M H c);
  *   one record per (chunk, head) of M H records, each 3 64 dk e + 2 64 64 e + 4 dk bytes
- *   rounded up to 256 (K_bar, Q_bar, P_tail^T, L^-1, A_qk, gamma_C),
+ *   rounded up to 256 (K_bar, Q_bar, P_tail^T L^-1, A_qk L^-1, gamma_C; 64 64 e unused),
  * about 1 KB per token and head for bf16 at dk = 128. It needs no initialisation and is dead
  * once the forward's work on the stream has finished; two forwards in flight at once need two.
  */

@@ -10,19 +10,20 @@
 //      log-depth scan of the summaries                               eq. chunk-gain-carry
 //   3. prep_kernel (chunk, head): replays the chunk from its carry (eqs. chunk-gain-local-prefix,
 //      chunk-gain-emission) and builds everything of the memory scan that does not depend on the
-//      memory state S: the decayed keys and queries, the tail-decayed write directions, the
-//      inverse of the triangular factor and the intra-chunk read matrix. One record per
-//      (chunk, head) in the workspace.
+//      memory state S: the decayed keys and queries, and, with the inverse of the triangular
+//      factor folded in, the write directions KA = L^-T P_tail and the intra-chunk read matrix
+//      BA = A_qk L^-1. One record per (chunk, head) in the workspace.
 //   4. walk_kernel (sequence, head, 32 value columns): carries S through the chunks in order:
-//        X = V - K_bar S,  R = L^-1 X,  O = scale (Q_bar S + A_qk R),  S <- gamma_C (.) S + P_tail^T R
-//      (eqs. chunk-memory-wy, chunk-memory-tail-output, chunk-memory-output-state).
+//        X = V - K_bar S,  O = scale (Q_bar S + BA X),  S <- gamma_C (.) S + KA^T X
+//      (eqs. chunk-memory-wy, chunk-memory-tail-output, chunk-memory-output-state with
+//      R = L^-1 X, the innovations, eliminated).
 //
 // Chunk algebra. With gamma_t = prod_{j <= t} alpha_j inside the chunk (per channel), the gain's
 // normalisation kappa_t = G_t (.) k_t / c_t (G = p_hat and c = r + sum_i p_hat_i k_i^2 for the
 // diagonal variant; G = beta and c = 1 for the isotropic one) is moved into the triangular
 // factor:  L = diag(c) + tril(M, -1),  M_ts = sum_i k_ti (gamma_t / gamma_s)_i G_si k_si,
 // A_qk = tril(M^q) with q in place of k (diagonal included: the read follows the write), and
-// row t of R is token t's innovation divided by c_t. The decay ratios gamma_t / gamma_s <= 1 are
+// row t of L^-1 X is token t's innovation divided by c_t. The decay ratios gamma_t / gamma_s <= 1 are
 // formed without any factor larger than one where possible (the paper forms them from
 // cumulative log-decay differences for the same reason):
 //   - products with S use K_bar = gamma (.) k and Q_bar = gamma (.) q (<= 1 per channel), and the
@@ -49,19 +50,20 @@ constexpr int NTH = 64 * NW;
 
 // Record the prep writes for the walk, per (chunk, head), in operand precision MT:
 //   Kb [C][DK]   K_bar = gamma (.) k            Qb [C][DK]  Q_bar = gamma (.) q
-//   Pt [DK][C]   P_tail^T                       Li [C][C]   L^-1 (zeros above the diagonal)
-//   Aq [C][C]    A_qk (zeros above)             gC [DK]     gamma_C (float32)
-// The five matrices are stored in MFMA-fragment order (frag_off), so that the walk reads
+//   Ka [DK][C]   KA^T = P_tail^T L^-1           Ba [C][C]   A_qk L^-1 (zeros above the diagonal)
+//   gC [DK]      gamma_C (float32)
+// The four matrices are stored in MFMA-fragment order (frag_off), so that the walk reads
 // every operand fragment as one contiguous block.
 template <class MT, int DK>
 struct OpRec {
     static constexpr size_t OFF_KB = 0;
     static constexpr size_t OFF_QB = OFF_KB + (size_t)C * DK * sizeof(MT);
-    static constexpr size_t OFF_PT = OFF_QB + (size_t)C * DK * sizeof(MT);
-    static constexpr size_t OFF_LI = OFF_PT + (size_t)DK * C * sizeof(MT);
-    static constexpr size_t OFF_AQ = OFF_LI + (size_t)C * C * sizeof(MT);
-    static constexpr size_t OFF_GC = OFF_AQ + (size_t)C * C * sizeof(MT);
-    static constexpr size_t BYTES = al256(OFF_GC + (size_t)DK * 4);
+    static constexpr size_t OFF_KA = OFF_QB + (size_t)C * DK * sizeof(MT);
+    static constexpr size_t OFF_BA = OFF_KA + (size_t)DK * C * sizeof(MT);
+    static constexpr size_t OFF_GC = OFF_BA + (size_t)C * C * sizeof(MT);
+    // a record's slot keeps the size it had with L^-1 in it (64 x 64 more): the workspace sizes
+    // that callers hold, and the calls that the fixed scratch admits, stay as they are
+    static constexpr size_t BYTES = al256(OFF_GC + (size_t)DK * 4 + (size_t)C * C * sizeof(MT));
 };
 
 // Fragment order of an R x K matrix (R and K multiples of 16) used as an MFMA A operand with
@@ -403,7 +405,7 @@ struct PrepCfg : VarCfg<TI, DK_, VARIANT_, APC_> {
     static constexpr size_t SZ_CC = al16((size_t)C * LDC * sizeof(MT));
     static constexpr size_t SZ_R = cmax(SZ_OP, SZ_CC);
     // operand tiles [C][LDK] (mid-referenced, then start/end-referenced); reused at the end
-    // as the staging of A_qk and L^-1 [C][LDC]
+    // for A_qk, L^-T [C][LDC] and P_tail^T in fragment order
     static constexpr size_t OFF_KA = 0, OFF_QA = SZ_R, OFF_PA = 2 * SZ_R;
     // L's lower blocks in float32 [NLB][16][LDL]; the blocks' Moebius products alias them
     static constexpr size_t SZ_LF = al16(cmax((size_t)NLB * 16 * LDL * 4, (size_t)NB * DK * 16));
@@ -484,9 +486,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
     char* rec = a.ops + ((size_t)g * H + h) * Rec::BYTES;
     MT* gKb = (MT*)(rec + Rec::OFF_KB);
     MT* gQb = (MT*)(rec + Rec::OFF_QB);
-    MT* gPt = (MT*)(rec + Rec::OFF_PT);
-    MT* gLi = (MT*)(rec + Rec::OFF_LI);
-    MT* gAq = (MT*)(rec + Rec::OFF_AQ);
+    MT* gKa = (MT*)(rec + Rec::OFF_KA);
+    MT* gBa = (MT*)(rec + Rec::OFF_BA);
     float* gC = (float*)(rec + Rec::OFF_GC);
 
     const Src sr = make_src<TI, CF>(a.in, h, ch);
@@ -628,35 +629,15 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
         }
     }
 
-    // ---- P_tail^T = (gamma_C / gamma_s) G_s k_s (record, fragment order); gamma_C -----------
-    {
-        float px[SL], py[SL];
-        float2 Q = Gt;
+    if (w == 0 && vact) {  // gamma_C
+        float2 gc = make_float2(1.f, 1.f);
 #pragma unroll
-        for (int j = SL - 1; j >= 0; --j) {
-            px[j] = pk[j].x * Q.x;
-            py[j] = pk[j].y * Q.y;
-            Q.x *= Af[j].x;
-            Q.y *= Af[j].y;
+        for (int b = 0; b < NB; ++b) {
+            const float2 gg = *reinterpret_cast<const float2*>(segG + b * DK + ch);
+            gc.x *= gg.x;
+            gc.y *= gg.y;
         }
-        if (vact) {
-            constexpr int E = Frag<MT, C>::KF / 4;
-#pragma unroll
-            for (int e = 0; e < SL; e += E) {
-                storeN<MT, E>(gPt + frag_off<MT, C>(ch, SL * w + e), px + e);
-                storeN<MT, E>(gPt + frag_off<MT, C>(ch + 1, SL * w + e), py + e);
-            }
-            if (w == 0) {
-                float2 gc = make_float2(1.f, 1.f);
-#pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    const float2 gg = *reinterpret_cast<const float2*>(segG + b * DK + ch);
-                    gc.x *= gg.x;
-                    gc.y *= gg.y;
-                }
-                *reinterpret_cast<float2*>(gC + ch) = gc;
-            }
-        }
+        *reinterpret_cast<float2*>(gC + ch) = gc;
     }
 
     // ---- diagonal blocks: operands referenced to the block midpoint ---------------------------
@@ -784,23 +765,41 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
     __syncthreads();
 
     // ---- L^-1 by columns of blocks (float32 MFMA): wave c takes block column c,
-    // Li_bc = -A_bb sum_{c <= j < b} L_bj Li_jc, Li_cc = A_cc. A_qk and L^-1 are staged in the
-    // operand area (now free) and written out in fragment order -------------------------------
+    // Li_bc = -A_bb sum_{c <= j < b} L_bj Li_jc, Li_cc = A_cc. A_qk, L^-T and P_tail^T go to the
+    // operand area (now free) as the operands of the two products below --------------------------
     MT* Aqs = Ka;  // [C][LDC]
-    MT* Lis = Qa;  // [C][LDC]
+    MT* LiT = Qa;  // [C][LDC]
+    MT* Pts = Pa;  // fragment order of [DK][C]
     {
         // A_qk: row block w (diagonal tile here, the off-diagonal tiles of this wave below,
         // zeros right of the diagonal)
-        auto put = [&](MT* dst, int ib, int jb, floatx4 v) {
+        auto put = [&](int ib, int jb, floatx4 v) {
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr)
-                dst[(16 * ib + 4 * lg + rr) * LDC + 16 * jb + li] = from_f32<MT>(v[rr]);
+                Aqs[(16 * ib + 4 * lg + rr) * LDC + 16 * jb + li] = from_f32<MT>(v[rr]);
         };
-        put(Aqs, w, w, aqd);
-        for (int jb = w + 1; jb < NB; ++jb) put(Aqs, w, jb, zero4());
+        put(w, w, aqd);
+        for (int jb = w + 1; jb < NB; ++jb) put(w, jb, zero4());
         if (w < 3) {
-            put(Aqs, oib[0], ojb[0], aqo[0]);
-            put(Aqs, oib[1], ojb[1], aqo[1]);
+            put(oib[0], ojb[0], aqo[0]);
+            put(oib[1], ojb[1], aqo[1]);
+        }
+        if (vact) {  // P_tail = (gamma_C / gamma_s) G_s k_s
+            constexpr int E = Frag<MT, C>::KF / 4;
+            float px[SL], py[SL];
+            float2 Q = Gt;
+#pragma unroll
+            for (int j = SL - 1; j >= 0; --j) {
+                px[j] = pk[j].x * Q.x;
+                py[j] = pk[j].y * Q.y;
+                Q.x *= Af[j].x;
+                Q.y *= Af[j].y;
+            }
+#pragma unroll
+            for (int e = 0; e < SL; e += E) {
+                storeN<MT, E>(Pts + frag_off<MT, C>(ch, SL * w + e), px + e);
+                storeN<MT, E>(Pts + frag_off<MT, C>(ch + 1, SL * w + e), py + e);
+            }
         }
         const int c = w;
         floatx4 lt[NB];
@@ -825,12 +824,47 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
                     acc);
                 lt[b][0] = -t[0]; lt[b][1] = -t[1]; lt[b][2] = -t[2]; lt[b][3] = -t[3];
             }
-            put(Lis, b, c, lt[b]);
+            store4<MT>(LiT + (16 * c + li) * LDC + 16 * b + 4 * lg, lt[b][0], lt[b][1], lt[b][2],
+                       lt[b][3]);
         }
     }
     __syncthreads();
-    copy_frag_order<MT, C, C, NTH>(gAq, Aqs, LDC, tid);
-    copy_frag_order<MT, C, C, NTH>(gLi, Lis, LDC, tid);
+    // ---- KA = L^-T P_tail and BA^T = L^-T A_qk^T, row block w: both contract over the rows of
+    // L^-1. A result tile holds four adjacent rows of a column: a piece (float32) or half a piece
+    // (bf16) of the fragment order of KA^T and BA, stored as it is ------------------------------
+    {
+        using FC = Frag<MT, C>;
+        constexpr int NKT = DK / 16;
+        // fragments left of the diagonal of L^-T's row block are zero
+        const int s0 = 16 * w / FC::KF;
+        typename FC::V lf[FC::NS];
+#pragma unroll
+        for (int s = 0; s < FC::NS; ++s)
+            lf[s] = FC::ld(LiT + (16 * w + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
+        auto put = [&](MT* base, int rb, floatx4 v) {
+            store4<MT>(base + frag_off<MT, C>(16 * rb + li, 16 * w + 4 * lg), v[0], v[1], v[2],
+                       v[3]);
+        };
+#pragma unroll
+        for (int ct = 0; ct < NKT; ++ct) {
+            floatx4 acc = zero4();
+#pragma unroll
+            for (int s = 0; s < FC::NS; ++s)
+                if (s >= s0) acc = FC::mma(acc, lf[s], FC::ld(frag_piece<MT, C>(Pts, ct, s, lane)));
+            put(gKa, ct, acc);
+        }
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) {
+            floatx4 acc = zero4();
+#pragma unroll
+            for (int s = 0; s < FC::NS; ++s)
+                if (s >= s0)
+                    acc = FC::mma(acc, lf[s],
+                                  FC::ld(Aqs + (16 * tb + li) * LDC + FC::KF * s +
+                                         (FC::KF / 4) * lg));
+            put(gBa, tb, acc);
+        }
+    }
     __syncthreads();
 
     // ---- K_bar = gamma (.) k and Q_bar = gamma (.) q (decay since the chunk start), staged in
@@ -868,6 +902,12 @@ void prep_layer_kernel(PrepArgs a)
 
 // ------------------------------------------------------------------------------------------
 // 4. walk: the memory state through the chunks of one (sequence, head, value tile)
+//
+// Bound by the latency of its serial chain, two barriers per chunk: S from LDS, X, X through LDS,
+// S. With L^-1 folded into the record (KA, BA) a chunk has no third product between X and S, its
+// record is 8 KB (of 64) smaller, and no load, store or tile sits in a branch: 150 us against 189 us
+// for 128 chunks alone (1.17 against 1.48 us per chunk: B1 T8191 H16 d128 bf16, 64 workgroups), 796
+// against 928 us for 134,000 packed tokens, 109 against 133 us at B4 T4096.
 // ------------------------------------------------------------------------------------------
 template <class TI, int DK_, int DV_>
 struct WalkCfg {
@@ -877,16 +917,21 @@ struct WalkCfg {
     static constexpr int NV = DV / BV;
     static constexpr int NNT = BV / 16, NKT = DK / 16, NST = NKT * NNT;
     static constexpr int SPW = (NST + NW - 1) / NW;  // S tiles per wave: x = SPW w + j
-    // tiles of a wave share their P_tail rows when the key tile is constant over NNT tiles
+    // tiles of a wave share their KA rows when the key tile is constant over NNT tiles
     static constexpr bool SHARE = SPW % NNT == 0;
     static constexpr int PPW = SHARE ? SPW / NNT : SPW;
+    // every wave has SPW tiles. Branches around a tile's products would split the loop into blocks
+    // that wait for their own results, and a load or store in one makes the other waits
+    // conservative (the newest loads instead of the oldest)
+    static constexpr bool EXACT = SPW * NW == NST;
+    // 16-byte pieces of the O tile per thread
+    static constexpr int VPR = BV * (int)sizeof(TI) / 16, NOP = (C * VPR + NTH - 1) / NTH;
     static constexpr int PAD = 16 / (int)sizeof(MT);
     static constexpr int LDK = DK + PAD, LDC = C + PAD;
     static constexpr int LDO = BV + 16 / (int)sizeof(TI);
     static constexpr size_t OFF_SMT = 0;                                       // S^T [BV][LDK]
     static constexpr size_t OFF_XT = al16((size_t)BV * LDK * sizeof(MT));      // X^T [BV][LDC]
-    static constexpr size_t OFF_RT = OFF_XT + al16((size_t)BV * LDC * sizeof(MT));  // R^T
-    static constexpr size_t OFF_O = OFF_RT + al16((size_t)BV * LDC * sizeof(MT));   // O [C][LDO]
+    static constexpr size_t OFF_O = OFF_XT + al16((size_t)BV * LDC * sizeof(MT));   // O [C][LDO]
     static constexpr size_t OFF_V = OFF_O + al16((size_t)C * LDO * sizeof(TI));     // V [C][LDO]
     static constexpr size_t TOTAL = al16(OFF_V + (size_t)C * LDO * sizeof(TI));
     // V tile of a chunk in 16-byte pieces: VPC per row; wave w moves the 16 rows of its own row
@@ -921,7 +966,6 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     extern __shared__ __attribute__((aligned(16))) char smem[];
     MT* SmT = (MT*)(smem + CF::OFF_SMT);
     MT* XT = (MT*)(smem + CF::OFF_XT);
-    MT* RT = (MT*)(smem + CF::OFF_RT);
     TI* Ost = (TI*)(smem + CF::OFF_O);
     TI* Vt = (TI*)(smem + CF::OFF_V);
 
@@ -939,7 +983,6 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     int t0, t1, g0, nch;
     seq_span(a.cm, n, t0, t1);
     seq_chunks<C>(a.cm, n, t0, t1, g0, nch);
-    TI* go = (TI*)a.o;
 
     const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -950,7 +993,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     for (int j = 0; j < SPW; ++j) {
         const int x = SPW * w + j;
         Sacc[j] = zero4();
-        if (x < NST) {
+        if (CF::EXACT || x < NST) {
             const int ik = x / NNT, nt = x % NNT;
             if (a.S0) {
                 const float* src = a.S0 + (size_t)nh * DK * DV;
@@ -977,9 +1020,9 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     // operands of the next chunk, loaded one step ahead of their use (fragment order: one
     // contiguous piece per lane)
     typename FK::V kf[NSK], qf[NSK];
-    typename FC::V lf[NSC], af[NSC], pf[PPW][NSC];
-    float4 gc[PPW];
-    uint4 vraw[CF::VPW];  // the wave's rows of the chunk's V tile, 16 bytes per piece
+    typename FC::V af[NSC], pf[PPW][NSC];
+    floatx4 gc[PPW];
+    uintx4 vraw[CF::VPW];  // the wave's rows of the chunk's V tile, 16 bytes per piece
     auto load1 = [&](int m) {
         const char* rec = recp(m);
         const MT* Kb = (const MT*)(rec + Rec::OFF_KB);
@@ -996,8 +1039,8 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
             const uint32_t r = (uint32_t)(16 * w + q / CF::VPC);
             const uint32_t cb = (uint32_t)(q % CF::VPC) * 16;
             vraw[u] = __builtin_bit_cast(
-                uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, (int)((c0 + r) * rowv + colv + cb),
-                                                             0, 0));
+                uintx4, __builtin_amdgcn_raw_buffer_load_b128(rv, (int)((c0 + r) * rowv + colv + cb),
+                                                              0, 0));
         }
     };
     // the wave's V rows to LDS: every wave reads only the rows it writes, and LDS operations of
@@ -1007,49 +1050,49 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
         for (int u = 0; u < CF::VPW; ++u) {
             const int q = lane + 64 * u;
             if (q < 16 * CF::VPC)
-                *reinterpret_cast<uint4*>(Vt + (16 * w + q / CF::VPC) * LDO +
+                *reinterpret_cast<uintx4*>(Vt + (16 * w + q / CF::VPC) * LDO +
                                           (q % CF::VPC) * (16 / es)) = vraw[u];
         }
     };
     auto load2 = [&](int m) {
-        const MT* Li = (const MT*)(recp(m) + Rec::OFF_LI);
-#pragma unroll
-        for (int s = 0; s < NSC; ++s) lf[s] = FC::ld(frag_piece<MT, C>(Li, w, s, lane));
-    };
-    auto load3 = [&](int m) {
         const char* rec = recp(m);
-        const MT* Aq = (const MT*)(rec + Rec::OFF_AQ);
+        const MT* Ba = (const MT*)(rec + Rec::OFF_BA);
 #pragma unroll
-        for (int s = 0; s < NSC; ++s) af[s] = FC::ld(frag_piece<MT, C>(Aq, w, s, lane));
+        for (int s = 0; s < NSC; ++s) af[s] = FC::ld(frag_piece<MT, C>(Ba, w, s, lane));
 #pragma unroll
         for (int p = 0; p < PPW; ++p) {
             const int ik = key_tile(p);
-            const MT* Pt = (const MT*)(rec + Rec::OFF_PT);
+            const MT* Kt = (const MT*)(rec + Rec::OFF_KA);
 #pragma unroll
-            for (int s = 0; s < NSC; ++s) pf[p][s] = FC::ld(frag_piece<MT, C>(Pt, ik, s, lane));
-            gc[p] = *reinterpret_cast<const float4*>((const float*)(rec + Rec::OFF_GC) +
+            for (int s = 0; s < NSC; ++s) pf[p][s] = FC::ld(frag_piece<MT, C>(Kt, ik, s, lane));
+            gc[p] = *reinterpret_cast<const floatx4*>((const float*)(rec + Rec::OFF_GC) +
                                                      16 * ik + 4 * lg);
         }
     };
     if (nch > 0) {
         load1(0);
         load2(0);
-        load3(0);
     }
     __syncthreads();
 
-    constexpr int VE = 16 / (int)sizeof(TI), VPR = BV / VE;
+    // the O rows of the chunk at cp, its first Lp: pieces past them get an offset past the
+    // descriptor's end and are dropped
+    const rsrc_t ro = make_rsrc(a.o, a.bytes_v);
+    auto store_o = [&](int cp, int Lp) __attribute__((always_inline)) {
+        constexpr int VE = 16 / (int)sizeof(TI), VPR = CF::VPR;
+#pragma unroll
+        for (int u = 0; u < CF::NOP; ++u) {
+            const int idx = tid + NTH * u, t = min(idx / VPR, C - 1), e = (idx % VPR) * VE;
+            const bool ok = idx < C * VPR && t < Lp;
+            const uint32_t off = (uint32_t)(cp + t) * rowv + colv + (uint32_t)e * es;
+            __builtin_amdgcn_raw_buffer_store_b128(
+                *reinterpret_cast<const uintx4*>(Ost + t * LDO + e), ro,
+                (int)(ok ? off : 0xFFFFFFF0u), 0, 0);
+        }
+    };
     for (int m = 0; m < nch; ++m) {
         const int c0 = t0 + m * C, L = min(C, t1 - c0);
-        // the previous chunk's O rows (a full chunk: only the last one can be partial)
-        if (m > 0) {
-            const int cp = c0 - C;
-            for (int idx = tid; idx < C * VPR; idx += NTH) {
-                const int t = idx / VPR, e = (idx % VPR) * VE;
-                *reinterpret_cast<uint4*>(go + ((size_t)(cp + t) * H + h) * DV + col0 + e) =
-                    *reinterpret_cast<const uint4*>(Ost + t * LDO + e);
-            }
-        }
+        store_o(c0 - C, m > 0 ? C : 0);  // the previous chunk's O rows (none before the first)
         store_v();
         // ---- X = V - K_bar S (to LDS, transposed); Q_bar S kept for the output --------------
         floatx4 Oacc[NNT];
@@ -1084,7 +1127,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
         }
         load1(m + 1);
         __syncthreads();
-        // ---- R = L^-1 X ---------------------------------------------------------------------
+        // ---- O = scale (Q_bar S + BA X); S <- gamma_C (.) S + KA^T X --------------------------
         {
             typename FC::V xf[NNT][NSC];
 #pragma unroll
@@ -1093,80 +1136,59 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
                 for (int s = 0; s < NSC; ++s)
                     xf[nt][s] = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
 #pragma unroll
-            for (int nt = 0; nt < NNT; ++nt) {
-                floatx4 racc = zero4();
+            for (int j = 0; j < SPW; ++j) {
+                const int x = SPW * w + j;
+                if (CF::EXACT || x < NST) {
+                    // with SHARE, x % NNT = j % NNT is known at compile time
+                    const int ik = x / NNT, nt = CF::SHARE ? j % NNT : x % NNT;
+                    const int p = CF::SHARE ? j / NNT : j;
+                    // the product is summed from zero, then joined: gamma_C, loaded last, is
+                    // waited for here and not at the chunk's start
+                    floatx4 up = zero4();
+                    static_assert(NNT <= 2, "value tiles of at most 32 columns");
+                    // with SHARE the value tile is a compile-time index into xf; otherwise the
+                    // fragment is read again from LDS (a runtime index would put xf in scratch)
 #pragma unroll
-                for (int s = 0; s < NSC; ++s) racc = FC::mma(racc, lf[s], xf[nt][s]);
-                store4<MT>(RT + (16 * nt + li) * LDC + 16 * w + 4 * lg, racc[0], racc[1],
-                           racc[2], racc[3]);
+                    for (int s = 0; s < NSC; ++s) {
+                        typename FC::V xv;
+                        if constexpr (CF::SHARE)
+                            xv = xf[j % NNT][s];
+                        else
+                            xv = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
+                        up = FC::mma(up, pf[p][s], xv);
+                    }
+                    Sacc[j][0] = fmaf(Sacc[j][0], gc[p][0], up[0]);
+                    Sacc[j][1] = fmaf(Sacc[j][1], gc[p][1], up[1]);
+                    Sacc[j][2] = fmaf(Sacc[j][2], gc[p][2], up[2]);
+                    Sacc[j][3] = fmaf(Sacc[j][3], gc[p][3], up[3]);
+                    store4<MT>(SmT + (16 * nt + li) * LDK + 16 * ik + 4 * lg, Sacc[j][0],
+                               Sacc[j][1], Sacc[j][2], Sacc[j][3]);
+                }
             }
-        }
-        load2(m + 1);
-        __syncthreads();
-        // ---- O = scale (Q_bar S + A_qk R); S <- gamma_C (.) S + P_tail^T R --------------------
-        {
-            typename FC::V rf[NNT][NSC];
-#pragma unroll
-            for (int nt = 0; nt < NNT; ++nt)
-#pragma unroll
-                for (int s = 0; s < NSC; ++s)
-                    rf[nt][s] = FC::ld(RT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt) {
 #pragma unroll
-                for (int s = 0; s < NSC; ++s) Oacc[nt] = FC::mma(Oacc[nt], af[s], rf[nt][s]);
+                for (int s = 0; s < NSC; ++s) Oacc[nt] = FC::mma(Oacc[nt], af[s], xf[nt][s]);
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)
                     Ost[(16 * w + 4 * lg + rr) * LDO + 16 * nt + li] =
                         from_f32<TI>(a.scale * Oacc[nt][rr]);
             }
-#pragma unroll
-            for (int j = 0; j < SPW; ++j) {
-                const int x = SPW * w + j;
-                if (x < NST) {
-                    // with SHARE, x % NNT = j % NNT is known at compile time
-                    const int ik = x / NNT, nt = CF::SHARE ? j % NNT : x % NNT;
-                    const int p = CF::SHARE ? j / NNT : j;
-                    Sacc[j][0] *= gc[p].x;
-                    Sacc[j][1] *= gc[p].y;
-                    Sacc[j][2] *= gc[p].z;
-                    Sacc[j][3] *= gc[p].w;
-                    static_assert(NNT <= 2, "value tiles of at most 32 columns");
-                    // with SHARE the value tile is a compile-time index into rf; otherwise the
-                    // fragment is read again from LDS (a runtime index would put rf in scratch)
-#pragma unroll
-                    for (int s = 0; s < NSC; ++s) {
-                        typename FC::V rv;
-                        if constexpr (CF::SHARE)
-                            rv = rf[j % NNT][s];
-                        else
-                            rv = FC::ld(RT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
-                        Sacc[j] = FC::mma(Sacc[j], pf[p][s], rv);
-                    }
-                    store4<MT>(SmT + (16 * nt + li) * LDK + 16 * ik + 4 * lg, Sacc[j][0],
-                               Sacc[j][1], Sacc[j][2], Sacc[j][3]);
-                }
-            }
         }
-        load3(m + 1);
+        load2(m + 1);
         __syncthreads();
     }
 
     if (nch > 0) {  // the last chunk's O rows
-        const int cp = t0 + (nch - 1) * C, Lp = t1 - cp;
-        for (int idx = tid; idx < C * VPR; idx += NTH) {
-            const int t = idx / VPR, e = (idx % VPR) * VE;
-            if (t < Lp)
-                *reinterpret_cast<uint4*>(go + ((size_t)(cp + t) * H + h) * DV + col0 + e) =
-                    *reinterpret_cast<const uint4*>(Ost + t * LDO + e);
-        }
+        const int cp = t0 + (nch - 1) * C;
+        store_o(cp, t1 - cp);
     }
     if (a.S_T) {
         float* dst = a.S_T + (size_t)nh * DK * DV;
 #pragma unroll
         for (int j = 0; j < SPW; ++j) {
             const int x = SPW * w + j;
-            if (x < NST) {
+            if (CF::EXACT || x < NST) {
                 const int ik = x / NNT, nt = x % NNT;
 #pragma unroll
                 for (int rr = 0; rr < 4; ++rr)

@@ -71,6 +71,17 @@ def test_forward_bf16_ragged(variant, apc):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dk,dv", [(16, 16), (32, 128), (128, 16), (128, 32)])
+@pytest.mark.parametrize("T", [1, 16, 65, 127])
+def test_forward_tile_edges(T, dk, dv, dtype):
+    """Chunks of one token, of whole 16-token blocks, one past and one short of a chunk, over heads
+    with fewer state tiles than waves and output tiles of 16 and 32 columns (rows past the end are
+    not stored: the tokens of the other sequence are checked with them)."""
+    x = W.draw_inputs("diag", dtype, 2, T, 3, dk, dv, seed=49, random_state=True)
+    compare_forward(x)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("variant", ["diag", "iso"])
 def test_forward_packed_ragged(variant, dtype):
     lens = [1, 63, 64, 0, 65, 130, 7]
