@@ -67,6 +67,18 @@ __device__ __forceinline__ floatx4 mm(floatx4 acc, floatx4 a, floatx4 b)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], acc, 0, 0, 0);
 }
 
+// N independent products step by step: a step on a result waits longer for the step before it than
+// the unit takes per step, so consecutive ones go to different results.
+template <int N>
+__device__ __forceinline__ void mmn(floatx4 (&acc)[N], const floatx4 (&a)[N], const floatx4 (&b)[N])
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[i][e], acc[i], 0, 0, 0);
+}
+
 // a * s + b. The products that join a running value are summed from zero and added here: summed
 // onto it, each of their steps would round at its size.
 __device__ __forceinline__ floatx4 fma4(floatx4 a, float s, floatx4 b)
@@ -80,11 +92,11 @@ __device__ __forceinline__ floatx4 fma4(floatx4 a, floatx4 s, floatx4 b)
                    fmaf(a[3], s[3], b[3])};
 }
 
-template <int N>
+template <int N, int STRIDE = 1>
 __device__ __forceinline__ floatx4 sum_parts(const floatx4* p)
 {
-    if constexpr (N == 4) return (p[0] + p[1]) + (p[2] + p[3]);
-    else if constexpr (N == 2) return p[0] + p[1];
+    if constexpr (N == 4) return (p[0] + p[STRIDE]) + (p[2 * STRIDE] + p[3 * STRIDE]);
+    else if constexpr (N == 2) return p[0] + p[STRIDE];
     else return p[0];
 }
 
@@ -684,9 +696,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 // operands are read straight into registers, one chunk ahead. At DK = 128, NJT = 2 a chunk is
 // 128 (forward) or up to 224 (reverse) MFMAs of 32 cycles per wave on its SIMD's matrix core.
 // Every load is unconditional: with one inside a branch the compiler has to assume it was not
-// issued and waits for the newest loads instead of the oldest. At B4 T4096 H16 d128 (one
-// workgroup per CU, 64 chunks in series): 272 and 379 us against 589 and 721 us with the operands
-// staged through LDS and L^-1 applied inside the walk (a third product and barrier per chunk).
+// issued and waits for the newest loads instead of the oldest. Each operand is fetched again right
+// after the step that used it, between the MFMAs: issued in one burst before the barrier, the four
+// waves' loads queue for the CU's one memory pipeline while no MFMA runs. At B4 T4096 H16 d128
+// (one workgroup per CU, 64 chunks in series): 210 and 312 us, against 272 and 393 us with bursts
+// and a product's dependent steps in sequence, and 589 and 721 us with the operands staged through
+// LDS and L^-1 applied inside the walk (a third product and barrier per chunk).
 // ------------------------------------------------------------------------------------------
 template <int DK, int NJT>
 struct WalkCfg {
@@ -757,10 +772,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
     float gc[KPW];
     typename Raw1<TI>::type vr[NJT][4];
     auto recp = [&](int m) { return a.rec + ((size_t)(g0 + min(m, nch - 1)) * H + h) * a.recn; };
-    auto load1 = [&](int m) __attribute__((always_inline)) {
-        const float* nk = recp(m) + R::NK + (size_t)w * NKT * 256;
-#pragma unroll
-        for (int s = 0; s < NKT; ++s) kf[s] = tile_rows(nk + 256 * s, li, lg);
+    auto load_k = [&](int m, int s) __attribute__((always_inline)) {
+        kf[s] = tile_rows(recp(m) + R::NK + (size_t)(w * NKT + s) * 256, li, lg);
+    };
+    auto load_v = [&](int m) __attribute__((always_inline)) {
         const uint32_t c0 = (uint32_t)(t0 + min(m, nch - 1) * C + 16 * w + 4 * lg);
 #pragma unroll
         for (int jt = 0; jt < NJT; ++jt)
@@ -768,18 +783,40 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
             for (int r = 0; r < 4; ++r)
                 vr[jt][r] = Raw1<TI>::load(rv, (c0 + r) * rowv + colv + 16 * jt * es);
     };
-    auto load2 = [&](int m) __attribute__((always_inline)) {
-        const float* rec = recp(m);
+    auto load_a = [&](int m, int tb) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < KPW; ++u) {
+        for (int u = 0; u < KPW; ++u)
+            ka[u][tb] = tile_cols(recp(m) + R::KA + (size_t)(tb * NKT + kt0 + u) * 256, li, lg);
+    };
+    auto load_g = [&](int m) __attribute__((always_inline)) {
 #pragma unroll
-            for (int tb = 0; tb < NB; ++tb)
-                ka[u][tb] = tile_cols(rec + R::KA + (size_t)(tb * NKT + kt0 + u) * 256, li, lg);
-            gc[u] = rec[R::GC + 16 * (kt0 + u) + li];
+        for (int u = 0; u < KPW; ++u) gc[u] = recp(m)[R::GC + 16 * (kt0 + u) + li];
+    };
+    // the state tiles' product: m [value][token] (LDS) with the wave's key tiles of a record matrix;
+    // reload(tb) fetches the next chunk's tiles of a step once it is done
+    auto state_prod = [&](floatx4 (&up)[KPW * NJT], const float* m, const floatx4 (&t)[KPW][NB],
+                          auto reload) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < KPW * NJT; ++i) up[i] = zero4();
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) {
+            floatx4 av[KPW * NJT], bv[KPW * NJT];
+#pragma unroll
+            for (int i = 0; i < KPW * NJT; ++i) {
+                av[i] = ldv(m + (16 * (i % NJT) + li) * LDC + 16 * tb + 4 * lg);
+                bv[i] = t[i / NJT][tb];
+            }
+            mmn(up, av, bv);
+            reload(tb);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
-    load1(0);
-    load2(0);
+#pragma unroll
+    for (int s = 0; s < NKT; ++s) load_k(0, s);
+    load_v(0);
+#pragma unroll
+    for (int tb = 0; tb < NB; ++tb) load_a(0, tb);
+    load_g(0);
     __syncthreads();
     for (int m = 0; m < nch; ++m) {
         const int L = min(C, t1 - (t0 + m * C));
@@ -793,50 +830,46 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
                         S[u][jt]);
         }
         // X = V - Kbar S_in, row block w
-        floatx4 x[NJT], xp[NJT][CF::NP];
+        // partial sums by key tile modulo NP, [NP][NJT]
+        floatx4 x[NJT], xp[CF::NP * NJT];
 #pragma unroll
-        for (int s = 0; s < NKT; ++s)
+        for (int i = 0; i < CF::NP * NJT; ++i) xp[i] = zero4();
 #pragma unroll
-            for (int jt = 0; jt < NJT; ++jt)
-                xp[jt][s % CF::NP] =
-                    mm(s < CF::NP ? zero4() : xp[jt][s % CF::NP], kf[s],
-                       ldv(s_S + (16 * jt + li) * LDK + 16 * s + 4 * lg));
+        for (int s = 0; s < NKT; s += CF::NP) {
+            floatx4 av[CF::NP * NJT], bv[CF::NP * NJT];
+#pragma unroll
+            for (int i = 0; i < CF::NP * NJT; ++i) {
+                const int st = s + i / NJT, jt = i % NJT;
+                av[i] = kf[st];
+                bv[i] = ldv(s_S + (16 * jt + li) * LDK + 16 * st + 4 * lg);
+            }
+            mmn(xp, av, bv);
+#pragma unroll
+            for (int i = 0; i < CF::NP; ++i) load_k(m + 1, s + i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int jt = 0; jt < NJT; ++jt) {
-            x[jt] = sum_parts<CF::NP>(xp[jt]);
+            x[jt] = sum_parts<CF::NP, NJT>(xp + jt);
 #pragma unroll
             for (int r = 0; r < 4; ++r)  // rows past the end of the sequence read as zeros
                 x[jt][r] += 16 * w + 4 * lg + r < L ? Raw1<TI>::f32(vr[jt][r]) : 0.f;
             stv(s_X + (16 * jt + li) * LDC + 16 * w + 4 * lg, x[jt]);
             stv(a.xt + (((gh * 4 + w) * NJ + vt * NJT + jt) * 64 + lane) * 4, x[jt]);
         }
-        load1(m + 1);
+        load_v(m + 1);
         __syncthreads();
         // S^T <- S^T diag(gamma_C) + X^T KA
         {
-            floatx4 up[KPW][NJT];
+            floatx4 up[KPW * NJT];
+            state_prod(up, s_X, ka, [&](int tb) { load_a(m + 1, tb); });
 #pragma unroll
             for (int u = 0; u < KPW; ++u)
 #pragma unroll
-                for (int jt = 0; jt < NJT; ++jt) up[u][jt] = zero4();
-#pragma unroll
-            for (int tb = 0; tb < NB; ++tb) {
-                floatx4 xf[NJT];
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt)
-                    xf[jt] = ldv(s_X + (16 * jt + li) * LDC + 16 * tb + 4 * lg);
-#pragma unroll
-                for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                    for (int jt = 0; jt < NJT; ++jt) up[u][jt] = mm(up[u][jt], xf[jt], ka[u][tb]);
-            }
-#pragma unroll
-            for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt) S[u][jt] = fma4(S[u][jt], gc[u], up[u][jt]);
+                for (int jt = 0; jt < NJT; ++jt) S[u][jt] = fma4(S[u][jt], gc[u], up[u * NJT + jt]);
             if (own) put_state();
         }
-        load2(m + 1);
+        load_g(m + 1);
         __syncthreads();
     }
 }
@@ -882,55 +915,91 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
     if (own) put_state();
     floatx4 ka[NKT], ba[NB], qb[KPW][NB], nk[KPW][NB];
     float gc[KPW];
-    TI ov[PER];  // dO as stored: converted when it is put to LDS
-    bool ovok = false;
+    // dO as stored, and a mask of its rows: both are read when it is put to LDS, without a branch
+    typedef unsigned OW __attribute__((ext_vector_type(PER * sizeof(TI) / 4)));
+    OW ow = {};
+    unsigned omask = 0;
     const rsrc_t rdv = make_rsrc(a.dv, a.bytes_dv);
     auto recp = [&](int m) { return a.rec + ((size_t)(g0 + max(m, 0)) * H + h) * a.recn; };
-    auto load1 = [&](int m) __attribute__((always_inline)) {
-        const float* rec = recp(m);
-#pragma unroll
-        for (int s = 0; s < NKT; ++s)
-            ka[s] = tile_rows(rec + R::KA + (size_t)(w * NKT + s) * 256, li, lg);
-#pragma unroll
-        for (int tb = 0; tb < NB; ++tb)
-            ba[tb] = ldv(rec + R::BA + ltile(max(tb, w), w) * 256 + 4 * lane);
+    auto load_a = [&](int m, int s) __attribute__((always_inline)) {
+        ka[s] = tile_rows(recp(m) + R::KA + (size_t)(w * NKT + s) * 256, li, lg);
+    };
+    auto load_b = [&](int m, int tb) __attribute__((always_inline)) {
+        ba[tb] = ldv(recp(m) + R::BA + ltile(max(tb, w), w) * 256 + 4 * lane);
+    };
+    auto load_o = [&](int m) __attribute__((always_inline)) {
         const int c0 = t0 + max(m, 0) * C, t = tid >> 2;
         const bool ok = a.dO && t < t1 - c0;
         // every thread loads: a row inside the sequence, v's where there is no dO
         const TI* p = (const TI*)(a.dO ? a.dO : a.v) +
                       ((size_t)(c0 + min(t, t1 - c0 - 1)) * H + h) * DV + j0 + PER * (tid & 3);
-        typedef TI TV __attribute__((ext_vector_type(16 / sizeof(TI) < PER ? 16 / sizeof(TI) : PER)));
-        constexpr int NE = sizeof(TV) / sizeof(TI);
-#pragma unroll
-        for (int e = 0; e < PER; e += NE) {
-            const TV x = *reinterpret_cast<const TV*>(p + e);
-#pragma unroll
-            for (int u = 0; u < NE; ++u) ov[e + u] = x[u];
-        }
-        ovok = ok;
+        __builtin_memcpy(&ow, __builtin_assume_aligned(p, sizeof(ow) < 16 ? sizeof(ow) : 16),
+                         sizeof(ow));
+        omask = ok ? ~0u : 0u;
     };
     auto put_o = [&]() __attribute__((always_inline)) {  // scale dO
 #pragma unroll
-        for (int e = 0; e < PER; ++e)
-            s_O[(PER * (tid & 3) + e) * LDC + (tid >> 2)] = ovok ? a.scale * (float)ov[e] : 0.f;
-    };
-    auto load2 = [&](int m) __attribute__((always_inline)) {
-        const float* rec = recp(m);
-#pragma unroll
-        for (int u = 0; u < KPW; ++u) {
-#pragma unroll
-            for (int tb = 0; tb < NB; ++tb) {
-                const size_t tl = (size_t)(tb * NKT + kt0 + u);
-                qb[u][tb] = ldv(rec + R::QB + (tl * 64 + lane) * 4);
-                nk[u][tb] = tile_cols(rec + R::NK + tl * 256, li, lg);
+        for (int e = 0; e < PER; ++e) {
+            float x;
+            if constexpr (sizeof(TI) == 4) {
+                x = __uint_as_float(ow[e] & omask);
+            } else {
+                const float2 y = unpack2(ow[e / 2] & omask);
+                x = e & 1 ? y.y : y.x;
             }
-            gc[u] = rec[R::GC + 16 * (kt0 + u) + li];
+            s_O[(PER * (tid & 3) + e) * LDC + (tid >> 2)] = a.scale * x;
+        }
+    };
+    auto load_q = [&](int m, int tb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < KPW; ++u)
+            qb[u][tb] = ldv(recp(m) + R::QB + ((size_t)(tb * NKT + kt0 + u) * 64 + lane) * 4);
+    };
+    auto load_k = [&](int m, int tb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < KPW; ++u)
+            nk[u][tb] = tile_cols(recp(m) + R::NK + (size_t)(tb * NKT + kt0 + u) * 256, li, lg);
+    };
+    auto load_g = [&](int m) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < KPW; ++u) gc[u] = recp(m)[R::GC + 16 * (kt0 + u) + li];
+    };
+    // the state tiles' product: m [value][token] (LDS) with the wave's key tiles of a record matrix;
+    // reload(tb) fetches the next chunk's tiles of a step once it is done
+    auto state_prod = [&](floatx4 (&up)[KPW * NJT], const float* m, const floatx4 (&t)[KPW][NB],
+                          auto reload) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < KPW * NJT; ++i) up[i] = zero4();
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) {
+            floatx4 av[KPW * NJT], bv[KPW * NJT];
+#pragma unroll
+            for (int i = 0; i < KPW * NJT; ++i) {
+                av[i] = ldv(m + (16 * (i % NJT) + li) * LDC + 16 * tb + 4 * lg);
+                bv[i] = t[i / NJT][tb];
+            }
+            mmn(up, av, bv);
+            reload(tb);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
     if (nch > 0) {
-        load1(nch - 1);
-        load2(nch - 1);
+        load_o(nch - 1);
         put_o();
+        __builtin_amdgcn_sched_barrier(0);
+        // in the loop's order: its waits cover the loads of both
+#pragma unroll
+        for (int s = 0; s < NKT; ++s) load_a(nch - 1, s);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) load_b(nch - 1, tb);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) load_q(nch - 1, tb);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tb = 0; tb < NB; ++tb) load_k(nch - 1, tb);
+        load_g(nch - 1);
     }
     __syncthreads();
     for (int m = nch - 1; m >= 0; --m) {
@@ -945,25 +1014,45 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
                         S[u][jt]);
         }
         // Psi = (A_qk L^-1)^T scale dO + KA dS_out = dV, row block w
-        floatx4 x[NJT], xp[NJT][CF::NP];
+        // partial sums by key tile modulo NP, [NP][NJT]
+        floatx4 x[NJT], xp[CF::NP * NJT];
 #pragma unroll
-        for (int s = 0; s < NKT; ++s)
+        for (int i = 0; i < CF::NP * NJT; ++i) xp[i] = zero4();
 #pragma unroll
-            for (int jt = 0; jt < NJT; ++jt)
-                xp[jt][s % CF::NP] =
-                    mm(s < CF::NP ? zero4() : xp[jt][s % CF::NP], ka[s],
-                       ldv(s_S + (16 * jt + li) * LDK + 16 * s + 4 * lg));
+        for (int s = 0; s < NKT; s += CF::NP) {
+            floatx4 av[CF::NP * NJT], bv[CF::NP * NJT];
 #pragma unroll
-        for (int jt = 0; jt < NJT; ++jt) x[jt] = zero4();
+            for (int i = 0; i < CF::NP * NJT; ++i) {
+                const int st = s + i / NJT, jt = i % NJT;
+                av[i] = ka[st];
+                bv[i] = ldv(s_S + (16 * jt + li) * LDK + 16 * st + 4 * lg);
+            }
+            mmn(xp, av, bv);
 #pragma unroll
-        for (int tb = 0; tb < NB; ++tb)
-            if (tb >= w)
+            for (int i = 0; i < CF::NP; ++i) load_a(m - 1, s + i);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // the tiles tb < w are zero (wave 0 has all four); two partial sums
+        floatx4 xo[2 * NJT];
 #pragma unroll
-                for (int jt = 0; jt < NJT; ++jt)
-                    x[jt] = mm(x[jt], ba[tb], ldv(s_O + (16 * jt + li) * LDC + 16 * tb + 4 * lg));
+        for (int i = 0; i < 2 * NJT; ++i) xo[i] = zero4();
+#pragma unroll
+        for (int tb = 0; tb < NB; tb += 2) {
+            floatx4 av[2 * NJT], bv[2 * NJT];
+#pragma unroll
+            for (int i = 0; i < 2 * NJT; ++i) {
+                const int t = tb + i / NJT, jt = i % NJT;
+                av[i] = t >= w ? ba[t] : zero4();
+                bv[i] = ldv(s_O + (16 * jt + li) * LDC + 16 * t + 4 * lg);
+            }
+            mmn(xo, av, bv);
+            load_b(m - 1, tb);
+            load_b(m - 1, tb + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int jt = 0; jt < NJT; ++jt) {
-            x[jt] += sum_parts<CF::NP>(xp[jt]);
+            x[jt] = xo[jt] + xo[NJT + jt] + sum_parts<CF::NP, NJT>(xp + jt);
             stv(s_P + (16 * jt + li) * LDC + 16 * w + 4 * lg, x[jt]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {  // rows past the end of the sequence are not stored
@@ -972,54 +1061,24 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
                           x[jt][r]);
             }
         }
-        load1(m - 1);
+        load_o(m - 1);
         // dS_in^T = dS_out^T diag(gamma_C) + (scale dO)^T Qbar - Psi^T Kbar; the dO term needs no
         // other wave's Psi and runs before the barrier
-        floatx4 uq[KPW][NJT];
-        {
-#pragma unroll
-            for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt) uq[u][jt] = zero4();
-#pragma unroll
-            for (int tb = 0; tb < NB; ++tb) {
-                floatx4 of[NJT];
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt)
-                    of[jt] = ldv(s_O + (16 * jt + li) * LDC + 16 * tb + 4 * lg);
-#pragma unroll
-                for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                    for (int jt = 0; jt < NJT; ++jt) uq[u][jt] = mm(uq[u][jt], of[jt], qb[u][tb]);
-            }
-        }
+        floatx4 uq[KPW * NJT];
+        state_prod(uq, s_O, qb, [&](int tb) { load_q(m - 1, tb); });
         __syncthreads();
         {
-            floatx4 up[KPW][NJT];
-#pragma unroll
-            for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt) up[u][jt] = zero4();
-#pragma unroll
-            for (int tb = 0; tb < NB; ++tb) {
-                floatx4 pf[NJT];
-#pragma unroll
-                for (int jt = 0; jt < NJT; ++jt)
-                    pf[jt] = ldv(s_P + (16 * jt + li) * LDC + 16 * tb + 4 * lg);
-#pragma unroll
-                for (int u = 0; u < KPW; ++u)
-#pragma unroll
-                    for (int jt = 0; jt < NJT; ++jt) up[u][jt] = mm(up[u][jt], pf[jt], nk[u][tb]);
-            }
+            floatx4 up[KPW * NJT];
+            state_prod(up, s_P, nk, [&](int tb) { load_k(m - 1, tb); });
 #pragma unroll
             for (int u = 0; u < KPW; ++u)
 #pragma unroll
                 for (int jt = 0; jt < NJT; ++jt)
-                    S[u][jt] = fma4(S[u][jt], gc[u], up[u][jt] + uq[u][jt]);
+                    S[u][jt] = fma4(S[u][jt], gc[u], up[u * NJT + jt] + uq[u * NJT + jt]);
             if (own) put_state();
         }
         put_o();
-        load2(m - 1);
+        load_g(m - 1);
         __syncthreads();
     }
     if (a.dS0 && own) {
@@ -1184,8 +1243,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
             for (int sb = 0; sb < NB; ++sb)
                 if (sb <= w) {
                     const floatx4 bD = ldv(s_D + ((sb * NJ + ks) * 64 + lane) * 4);
-                    p1[sb] += mm(zero4(), aO, bD);
-                    p2[sb] += mm(zero4(), aP, bD);
+                    floatx4 t2[2] = {zero4(), zero4()};
+                    mmn(t2, {aO, aP}, {bD, bD});
+                    p1[sb] += t2[0];
+                    p2[sb] += t2[1];
                 }
         }
 #pragma unroll
@@ -1217,9 +1278,11 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
                 // (without a branch: one here splits the loop and its registers)
                 const float s = fmaf(x[3], y[3], fmaf(x[2], y[2], fmaf(x[1], y[1], x[0] * y[0])));
                 (k < 4 ? p6 : p6b) += (k & 3) == w ? s : 0.f;
-                p3[k] += mm(zero4(), aP, x);
-                p4[k] += mm(zero4(), aO, x);
-                p5[k] += mm(zero4(), aD, y);
+                floatx4 t3[3] = {zero4(), zero4(), zero4()};
+                mmn(t3, {aP, aO, aD}, {x, x, y});
+                p3[k] += t3[0];
+                p4[k] += t3[1];
+                p5[k] += t3[2];
                 sv[k] = ldv(ps + (size_t)(k * NJ + kn) * 256);
                 gv[k] = ldv(pg + (size_t)(k * NJ + kn) * 256);
             }
