@@ -234,6 +234,16 @@ template <> __device__ __forceinline__ float2 bload<float2>(rsrc_t r, uint32_t o
     return make_float2(__uint_as_float(u[0]), __uint_as_float(u[1]));
 }
 
+// 8 or 16 bytes at a vector offset plus a scalar one.
+template <class V>
+__device__ __forceinline__ V bload_v(rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    if constexpr (sizeof(V) == 16)
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
+    else
+        return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0));
+}
+
 // One stored value held in a register of its own: a bf16 is kept zero-extended in 32 bits, so
 // values loaded ahead are never packed two to a register (packing would wait for the load).
 template <class TI> struct Raw1;

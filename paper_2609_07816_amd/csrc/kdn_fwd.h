@@ -49,7 +49,7 @@ constexpr int NW = 4;       // waves per workgroup
 constexpr int NTH = 64 * NW;
 
 // Record the prep writes for the walk, per (chunk, head), in operand precision MT:
-//   Kb [C][DK]   K_bar = gamma (.) k            Qb [C][DK]  Q_bar = gamma (.) q
+//   Kb [C][DK]   -K_bar = -gamma (.) k          Qb [C][DK]  Q_bar = gamma (.) q
 //   Ka [DK][C]   KA^T = P_tail^T L^-1           Ba [C][C]   A_qk L^-1 (zeros above the diagonal)
 //   gC [DK]      gamma_C (float32)
 // The four matrices are stored in MFMA-fragment order (frag_off), so that the walk reads
@@ -867,7 +867,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
     }
     __syncthreads();
 
-    // ---- K_bar = gamma (.) k and Q_bar = gamma (.) q (decay since the chunk start), staged in
+    // ---- -K_bar = -gamma (.) k and Q_bar = gamma (.) q (decay since the chunk start), staged in
     // the operand area and written out in fragment order --------------------------------------
     if (vact) {
         float2 P = Gs;
@@ -876,7 +876,7 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
             const int t = SL * w + j;
             P.x *= Af[j].x;
             P.y *= Af[j].y;
-            st2<MT>(Ka + t * LDK + ch, Kf[j].x * P.x, Kf[j].y * P.y);
+            st2<MT>(Ka + t * LDK + ch, -Kf[j].x * P.x, -Kf[j].y * P.y);
             st2<MT>(Qa + t * LDK + ch, Qf[j].x * P.x, Qf[j].y * P.y);
         }
     }
@@ -924,8 +924,6 @@ struct WalkCfg {
     // that wait for their own results, and a load or store in one makes the other waits
     // conservative (the newest loads instead of the oldest)
     static constexpr bool EXACT = SPW * NW == NST;
-    // 16-byte pieces of the O tile per thread
-    static constexpr int VPR = BV * (int)sizeof(TI) / 16, NOP = (C * VPR + NTH - 1) / NTH;
     static constexpr int PAD = 16 / (int)sizeof(MT);
     static constexpr int LDK = DK + PAD, LDC = C + PAD;
     static constexpr int LDO = BV + 16 / (int)sizeof(TI);
@@ -934,7 +932,7 @@ struct WalkCfg {
     static constexpr size_t OFF_O = OFF_XT + al16((size_t)BV * LDC * sizeof(MT));   // O [C][LDO]
     static constexpr size_t OFF_V = OFF_O + al16((size_t)C * LDO * sizeof(TI));     // V [C][LDO]
     static constexpr size_t TOTAL = al16(OFF_V + (size_t)C * LDO * sizeof(TI));
-    // V tile of a chunk in 16-byte pieces: VPC per row; wave w moves the 16 rows of its own row
+    // V or O tile of a chunk in 16-byte pieces: VPC per row; wave w moves the 16 rows of its own row
     // block (16 VPC pieces), VPW per lane
     static constexpr int VPC = BV * (int)sizeof(TI) / 16;
     static constexpr int VPW = (16 * VPC + 63) / 64;
@@ -1017,35 +1015,52 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     auto key_tile = [&](int p) { return min(CF::SHARE ? SPW * w / NNT + p : (SPW * w + p) / NNT,
                                             CF::NKT - 1); };
 
-    // operands of the next chunk, loaded one step ahead of their use (fragment order: one
-    // contiguous piece per lane)
+    // record operands, each fetched for the next chunk right after its use (fragment order: one
+    // contiguous piece per lane), between the products: issued together before a barrier, the
+    // four waves' loads would queue for the CU's memory pipeline while no product runs
     typename FK::V kf[NSK], qf[NSK];
     typename FC::V af[NSC], pf[PPW][NSC];
     floatx4 gc[PPW];
     uintx4 vraw[CF::VPW];  // the wave's rows of the chunk's V tile, 16 bytes per piece
-    auto load1 = [&](int m) {
-        const char* rec = recp(m);
-        const MT* Kb = (const MT*)(rec + Rec::OFF_KB);
-        const MT* Qb = (const MT*)(rec + Rec::OFF_QB);
+    // (a descriptor per record: the address arithmetic stays on the scalar unit)
+    auto rec_rsrc = [&](int m) { return make_rsrc(recp(m), (uint32_t)Rec::BYTES); };
+    constexpr uint32_t FKB = 64 * sizeof(typename FK::V), FCB = 64 * sizeof(typename FC::V);
+    const uint32_t lk = lane * sizeof(typename FK::V), lc = lane * sizeof(typename FC::V);
+    auto load_k = [&](int m, int s) __attribute__((always_inline)) {
+        kf[s] = bload_v<typename FK::V>(rec_rsrc(m), lk + s * FKB, Rec::OFF_KB + w * NSK * FKB);
+    };
+    auto load_q = [&](int m, int s) __attribute__((always_inline)) {
+        qf[s] = bload_v<typename FK::V>(rec_rsrc(m), lk + s * FKB, Rec::OFF_QB + w * NSK * FKB);
+    };
+    auto load_b = [&](int m) __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NSK; ++s) {
-            kf[s] = FK::ld(frag_piece<MT, DK>(Kb, w, s, lane));
-            qf[s] = FK::ld(frag_piece<MT, DK>(Qb, w, s, lane));
-        }
-        const uint32_t c0 = (uint32_t)(t0 + min(m, max(nch - 1, 0)) * C);
+        for (int s = 0; s < NSC; ++s)
+            af[s] = bload_v<typename FC::V>(rec_rsrc(m), lc + s * FCB, Rec::OFF_BA + w * NSC * FCB);
+    };
+    auto load_a = [&](int m, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < PPW; ++p)
+            pf[p][s] = bload_v<typename FC::V>(rec_rsrc(m), lc + s * FCB,
+                                               Rec::OFF_KA + key_tile(p) * NSC * FCB);
+    };
+    auto load_g = [&](int m) __attribute__((always_inline)) {
+#pragma unroll
+        for (int p = 0; p < PPW; ++p)
+            gc[p] = bload_v<floatx4>(rec_rsrc(m), 16 * lg, Rec::OFF_GC + 64 * key_tile(p));
+    };
+    auto load_v = [&](int m) __attribute__((always_inline)) {
+        // rows past the end of the sequence read as zeros: an offset past the descriptor's end
+        const int c0 = t0 + m * C;
 #pragma unroll
         for (int u = 0; u < CF::VPW; ++u) {
-            const int q = min(lane + 64 * u, 16 * CF::VPC - 1);
-            const uint32_t r = (uint32_t)(16 * w + q / CF::VPC);
-            const uint32_t cb = (uint32_t)(q % CF::VPC) * 16;
-            vraw[u] = __builtin_bit_cast(
-                uintx4, __builtin_amdgcn_raw_buffer_load_b128(rv, (int)((c0 + r) * rowv + colv + cb),
-                                                              0, 0));
+            const int q = min(lane + 64 * u, 16 * CF::VPC - 1), t = c0 + 16 * w + q / CF::VPC;
+            const uint32_t off = (uint32_t)t * rowv + colv + (uint32_t)(q % CF::VPC) * 16;
+            vraw[u] = bload_v<uintx4>(rv, t < t1 ? off : 0xFFFFFFF0u, 0);
         }
     };
-    // the wave's V rows to LDS: every wave reads only the rows it writes, and LDS operations of
-    // one wave run in order, so no barrier is needed between this and their use
-    auto store_v = [&]() {
+    // V and O pass through LDS by rows of the wave's own row block: LDS operations of one wave run
+    // in order, so no barrier stands between a store and its reads
+    auto store_v = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CF::VPW; ++u) {
             const int q = lane + 64 * u;
@@ -1054,133 +1069,182 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
                                           (q % CF::VPC) * (16 / es)) = vraw[u];
         }
     };
-    auto load2 = [&](int m) {
-        const char* rec = recp(m);
-        const MT* Ba = (const MT*)(rec + Rec::OFF_BA);
+    const rsrc_t ro = make_rsrc(a.o, a.bytes_v);
+    uintx4 oraw[CF::VPW];
+    auto read_o = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int s = 0; s < NSC; ++s) af[s] = FC::ld(frag_piece<MT, C>(Ba, w, s, lane));
-#pragma unroll
-        for (int p = 0; p < PPW; ++p) {
-            const int ik = key_tile(p);
-            const MT* Kt = (const MT*)(rec + Rec::OFF_KA);
-#pragma unroll
-            for (int s = 0; s < NSC; ++s) pf[p][s] = FC::ld(frag_piece<MT, C>(Kt, ik, s, lane));
-            gc[p] = *reinterpret_cast<const floatx4*>((const float*)(rec + Rec::OFF_GC) +
-                                                     16 * ik + 4 * lg);
+        for (int u = 0; u < CF::VPW; ++u) {
+            const int q = min(lane + 64 * u, 16 * CF::VPC - 1);
+            oraw[u] = *reinterpret_cast<const uintx4*>(Ost + (16 * w + q / CF::VPC) * LDO +
+                                                       (q % CF::VPC) * (16 / es));
         }
     };
+    // the O rows of the chunk at cp, its first Lp: pieces past them get an offset past the
+    // descriptor's end and are dropped
+    auto store_o = [&](int cp, int Lp) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < CF::VPW; ++u) {
+            const int q = lane + 64 * u, t = 16 * w + q / CF::VPC;
+            const uint32_t off =
+                (uint32_t)(cp + t) * rowv + colv + (uint32_t)(q % CF::VPC) * 16;
+            __builtin_amdgcn_raw_buffer_store_b128(
+                oraw[u], ro, (int)(q < 16 * CF::VPC && t < Lp ? off : 0xFFFFFFF0u), 0, 0);
+        }
+    };
+    floatx4 Oacc[NNT];
+    typename FC::V xf[NNT][NSC];
+#pragma unroll
+    for (int nt = 0; nt < NNT; ++nt) {
+        Oacc[nt] = zero4();
+#pragma unroll
+        for (int s = 0; s < NSC; ++s) xf[nt][s] = typename FC::V{};
+    }
+#pragma unroll
+    for (int s = 0; s < NSC; ++s) af[s] = typename FC::V{};
+    // O = scale (Q_bar S + BA X) of the chunk whose X fragments are held, to LDS; transposed (value
+    // rows, token columns), so that a lane's four values are adjacent
+    auto put_o = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < NSC; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NNT; ++nt) Oacc[nt] = FC::mma(Oacc[nt], xf[nt][s], af[s]);
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt)
+            store4<TI>(Ost + (16 * w + li) * LDO + 16 * nt + 4 * lg, a.scale * Oacc[nt][0],
+                       a.scale * Oacc[nt][1], a.scale * Oacc[nt][2], a.scale * Oacc[nt][3]);
+    };
     if (nch > 0) {
-        load1(0);
-        load2(0);
+        load_v(0);
+#pragma unroll
+        for (int s = 0; s < NSK; ++s) load_k(0, s);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NSK; ++s) load_q(0, s);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NSC; ++s) load_a(0, s);
+        load_g(0);
     }
     __syncthreads();
 
-    // the O rows of the chunk at cp, its first Lp: pieces past them get an offset past the
-    // descriptor's end and are dropped
-    const rsrc_t ro = make_rsrc(a.o, a.bytes_v);
-    auto store_o = [&](int cp, int Lp) __attribute__((always_inline)) {
-        constexpr int VE = 16 / (int)sizeof(TI), VPR = CF::VPR;
-#pragma unroll
-        for (int u = 0; u < CF::NOP; ++u) {
-            const int idx = tid + NTH * u, t = min(idx / VPR, C - 1), e = (idx % VPR) * VE;
-            const bool ok = idx < C * VPR && t < Lp;
-            const uint32_t off = (uint32_t)(cp + t) * rowv + colv + (uint32_t)e * es;
-            __builtin_amdgcn_raw_buffer_store_b128(
-                *reinterpret_cast<const uintx4*>(Ost + t * LDO + e), ro,
-                (int)(ok ? off : 0xFFFFFFF0u), 0, 0);
-        }
-    };
+    // Between the barriers stands only what the next S needs: X from S, S from X. The rest fills
+    // the waits for LDS: O of the chunk before while S is read, Q_bar S while X is read.
     for (int m = 0; m < nch; ++m) {
-        const int c0 = t0 + m * C, L = min(C, t1 - c0);
-        store_o(c0 - C, m > 0 ? C : 0);  // the previous chunk's O rows (none before the first)
+        const int c0 = t0 + m * C;
+        // ---- X = V - K_bar S (to LDS, transposed; the record holds -K_bar) ------------------
+        typename FK::V sf[NNT][NSK];
+#pragma unroll
+        for (int s = 0; s < NSK; ++s)
+#pragma unroll
+            for (int nt = 0; nt < NNT; ++nt)
+                sf[nt][s] = FK::ld(SmT + (16 * nt + li) * LDK + FK::KF * s + (FK::KF / 4) * lg);
         store_v();
-        // ---- X = V - K_bar S (to LDS, transposed); Q_bar S kept for the output --------------
-        floatx4 Oacc[NNT];
+        load_v(m + 1);
+        floatx4 vr[NNT];
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt)
+#pragma unroll
+            for (int rr = 0; rr < 4; ++rr)
+                vr[nt][rr] = to_f32(Vt[(16 * w + 4 * lg + rr) * LDO + 16 * nt + li]);
+        put_o();  // the chunk before (none before the first: dropped by store_o)
+        load_b(m);
+        __builtin_amdgcn_sched_barrier(0);
         {
-            typename FK::V sf[NNT][NSK];
+            // float32: the product is summed from zero, in two parts, and V joined after it, so
+            // that its roundings stay at its own size; bf16 operands need neither
+            constexpr int NP = sizeof(MT) == 4 ? 2 : 1;
+            floatx4 xacc[NNT][NP];
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt)
 #pragma unroll
-                for (int s = 0; s < NSK; ++s)
-                    sf[nt][s] = FK::ld(SmT + (16 * nt + li) * LDK + FK::KF * s + (FK::KF / 4) * lg);
+                for (int i = 0; i < NP; ++i) xacc[nt][i] = NP == 1 ? vr[nt] : zero4();
+#pragma unroll
+            for (int s = 0; s < NSK; ++s) {
+#pragma unroll
+                for (int nt = 0; nt < NNT; ++nt)
+                    xacc[nt][s % NP] = FK::mma(xacc[nt][s % NP], kf[s], sf[nt][s]);
+                load_k(m + 1, s);
+            }
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt) {
-                floatx4 xacc = zero4();
-                Oacc[nt] = zero4();
-#pragma unroll
-                for (int s = 0; s < NSK; ++s) {
-                    xacc = FK::mma(xacc, kf[s], sf[nt][s]);
-                    Oacc[nt] = FK::mma(Oacc[nt], qf[s], sf[nt][s]);
-                }
-                // rows past the end of the sequence hold another sequence's V or stale data:
-                // every row is read (no divergent reads), then masked
-                float vr[4], xv[4];
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    vr[rr] = to_f32(Vt[(16 * w + 4 * lg + rr) * LDO + 16 * nt + li]);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    xv[rr] = (16 * w + 4 * lg + rr < L ? vr[rr] : 0.f) - xacc[rr];
-                store4<MT>(XT + (16 * nt + li) * LDC + 16 * w + 4 * lg, xv[0], xv[1], xv[2],
-                           xv[3]);
+                const floatx4 x = NP == 1 ? xacc[nt][0] : (xacc[nt][0] + xacc[nt][NP - 1]) + vr[nt];
+                store4<MT>(XT + (16 * nt + li) * LDC + 16 * w + 4 * lg, x[0], x[1], x[2], x[3]);
             }
         }
-        load1(m + 1);
+        // Q_bar S for the output
+        auto q_s = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int nt = 0; nt < NNT; ++nt) Oacc[nt] = zero4();
+#pragma unroll
+            for (int s = 0; s < NSK; ++s) {
+#pragma unroll
+                for (int nt = 0; nt < NNT; ++nt) Oacc[nt] = FK::mma(Oacc[nt], sf[nt][s], qf[s]);
+                load_q(m + 1, s);
+            }
+        };
+        // float32: before the barrier, so that the fragments of S (64 registers) die there
+        constexpr bool LATEQ = sizeof(MT) == 2;
+        if constexpr (!LATEQ) q_s();
         __syncthreads();
-        // ---- O = scale (Q_bar S + BA X); S <- gamma_C (.) S + KA^T X --------------------------
-        {
-            typename FC::V xf[NNT][NSC];
+        // ---- S <- gamma_C (.) S + KA^T X ---------------------------------------------------
+#pragma unroll
+        for (int s = 0; s < NSC; ++s)
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt)
+                xf[nt][s] = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
+        read_o();
+        if constexpr (LATEQ) q_s();
+        __builtin_amdgcn_sched_barrier(0);
+        {
+            // the product is summed from zero, then joined: gamma_C, loaded last, is waited for
+            // here and not at the chunk's start
+            floatx4 up[SPW];
 #pragma unroll
-                for (int s = 0; s < NSC; ++s)
-                    xf[nt][s] = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
+            for (int j = 0; j < SPW; ++j) up[j] = zero4();
 #pragma unroll
-            for (int j = 0; j < SPW; ++j) {
-                const int x = SPW * w + j;
-                if (CF::EXACT || x < NST) {
-                    // with SHARE, x % NNT = j % NNT is known at compile time
-                    const int ik = x / NNT, nt = CF::SHARE ? j % NNT : x % NNT;
-                    const int p = CF::SHARE ? j / NNT : j;
-                    // the product is summed from zero, then joined: gamma_C, loaded last, is
-                    // waited for here and not at the chunk's start
-                    floatx4 up = zero4();
-                    static_assert(NNT <= 2, "value tiles of at most 32 columns");
-                    // with SHARE the value tile is a compile-time index into xf; otherwise the
-                    // fragment is read again from LDS (a runtime index would put xf in scratch)
+            for (int s = 0; s < NSC; ++s) {
 #pragma unroll
-                    for (int s = 0; s < NSC; ++s) {
+                for (int j = 0; j < SPW; ++j) {
+                    const int x = SPW * w + j;
+                    if (CF::EXACT || x < NST) {
+                        // with SHARE the value tile is a compile-time index into xf; otherwise
+                        // the fragment is read again from LDS (a runtime index would put xf in
+                        // scratch)
+                        static_assert(NNT <= 2, "value tiles of at most 32 columns");
                         typename FC::V xv;
                         if constexpr (CF::SHARE)
                             xv = xf[j % NNT][s];
                         else
-                            xv = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
-                        up = FC::mma(up, pf[p][s], xv);
+                            xv = FC::ld(XT + (16 * (x % NNT) + li) * LDC + FC::KF * s +
+                                        (FC::KF / 4) * lg);
+                        up[j] = FC::mma(up[j], pf[CF::SHARE ? j / NNT : j][s], xv);
                     }
-                    Sacc[j][0] = fmaf(Sacc[j][0], gc[p][0], up[0]);
-                    Sacc[j][1] = fmaf(Sacc[j][1], gc[p][1], up[1]);
-                    Sacc[j][2] = fmaf(Sacc[j][2], gc[p][2], up[2]);
-                    Sacc[j][3] = fmaf(Sacc[j][3], gc[p][3], up[3]);
+                }
+                load_a(m + 1, s);
+            }
+#pragma unroll
+            for (int j = 0; j < SPW; ++j) {
+                const int x = SPW * w + j;
+                if (CF::EXACT || x < NST) {
+                    const int ik = x / NNT, nt = CF::SHARE ? j % NNT : x % NNT;
+                    const int p = CF::SHARE ? j / NNT : j;
+#pragma unroll
+                    for (int rr = 0; rr < 4; ++rr)
+                        Sacc[j][rr] = fmaf(Sacc[j][rr], gc[p][rr], up[j][rr]);
                     store4<MT>(SmT + (16 * nt + li) * LDK + 16 * ik + 4 * lg, Sacc[j][0],
                                Sacc[j][1], Sacc[j][2], Sacc[j][3]);
                 }
             }
-#pragma unroll
-            for (int nt = 0; nt < NNT; ++nt) {
-#pragma unroll
-                for (int s = 0; s < NSC; ++s) Oacc[nt] = FC::mma(Oacc[nt], af[s], xf[nt][s]);
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    Ost[(16 * w + 4 * lg + rr) * LDO + 16 * nt + li] =
-                        from_f32<TI>(a.scale * Oacc[nt][rr]);
-            }
         }
-        load2(m + 1);
+        load_g(m + 1);
+        store_o(c0 - C, m > 0 ? C : 0);
         __syncthreads();
     }
 
     if (nch > 0) {  // the last chunk's O rows
         const int cp = t0 + (nch - 1) * C;
+        put_o();
+        read_o();
         store_o(cp, t1 - cp);
     }
     if (a.S_T) {
