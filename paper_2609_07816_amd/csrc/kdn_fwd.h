@@ -924,12 +924,12 @@ struct WalkCfg {
     // that wait for their own results, and a load or store in one makes the other waits
     // conservative (the newest loads instead of the oldest)
     static constexpr bool EXACT = SPW * NW == NST;
-    static constexpr int PAD = 16 / (int)sizeof(MT);
-    static constexpr int LDK = DK + PAD, LDC = C + PAD;
     static constexpr int LDO = BV + 16 / (int)sizeof(TI);
-    static constexpr size_t OFF_SMT = 0;                                       // S^T [BV][LDK]
-    static constexpr size_t OFF_XT = al16((size_t)BV * LDK * sizeof(MT));      // X^T [BV][LDC]
-    static constexpr size_t OFF_O = OFF_XT + al16((size_t)BV * LDC * sizeof(MT));   // O [C][LDO]
+    // S^T and X^T in fragment order: every fragment read is one contiguous KB, free of bank
+    // conflicts (rows padded to 16 bytes cost 384 cycles of conflicts per chunk in all)
+    static constexpr size_t OFF_SMT = 0;                                       // S^T [BV][DK]
+    static constexpr size_t OFF_XT = al16((size_t)BV * DK * sizeof(MT));       // X^T [BV][C]
+    static constexpr size_t OFF_O = OFF_XT + al16((size_t)BV * C * sizeof(MT));     // O [C][LDO]
     static constexpr size_t OFF_V = OFF_O + al16((size_t)C * LDO * sizeof(TI));     // V [C][LDO]
     static constexpr size_t TOTAL = al16(OFF_V + (size_t)C * LDO * sizeof(TI));
     // V or O tile of a chunk in 16-byte pieces: VPC per row; wave w moves the 16 rows of its own row
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     using FK = Frag<MT, CF::DK>;
     using FC = Frag<MT, C>;
     constexpr int DK = CF::DK, DV = CF::DV, BV = CF::BV, NNT = CF::NNT, NST = CF::NST;
-    constexpr int SPW = CF::SPW, PPW = CF::PPW, LDK = CF::LDK, LDC = CF::LDC, LDO = CF::LDO;
+    constexpr int SPW = CF::SPW, PPW = CF::PPW, LDO = CF::LDO;
     constexpr int NSK = FK::NS, NSC = FC::NS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     MT* SmT = (MT*)(smem + CF::OFF_SMT);
@@ -999,8 +999,8 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
                 for (int rr = 0; rr < 4; ++rr)
                     Sacc[j][rr] = src[(size_t)(16 * ik + 4 * lg + rr) * DV + col0 + 16 * nt + li];
             }
-            store4<MT>(SmT + (16 * nt + li) * LDK + 16 * ik + 4 * lg, Sacc[j][0], Sacc[j][1],
-                       Sacc[j][2], Sacc[j][3]);
+            store4<MT>(SmT + frag_off<MT, DK>(16 * nt + li, 16 * ik + 4 * lg), Sacc[j][0],
+                       Sacc[j][1], Sacc[j][2], Sacc[j][3]);
         }
     }
 
@@ -1137,7 +1137,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
         for (int s = 0; s < NSK; ++s)
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt)
-                sf[nt][s] = FK::ld(SmT + (16 * nt + li) * LDK + FK::KF * s + (FK::KF / 4) * lg);
+                sf[nt][s] = FK::ld(frag_piece<MT, DK>(SmT, nt, s, lane));
         store_v();
         load_v(m + 1);
         floatx4 vr[NNT];
@@ -1168,7 +1168,8 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt) {
                 const floatx4 x = NP == 1 ? xacc[nt][0] : (xacc[nt][0] + xacc[nt][NP - 1]) + vr[nt];
-                store4<MT>(XT + (16 * nt + li) * LDC + 16 * w + 4 * lg, x[0], x[1], x[2], x[3]);
+                store4<MT>(XT + frag_off<MT, C>(16 * nt + li, 16 * w + 4 * lg), x[0], x[1], x[2],
+                           x[3]);
             }
         }
         // Q_bar S for the output
@@ -1191,7 +1192,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
         for (int s = 0; s < NSC; ++s)
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt)
-                xf[nt][s] = FC::ld(XT + (16 * nt + li) * LDC + FC::KF * s + (FC::KF / 4) * lg);
+                xf[nt][s] = FC::ld(frag_piece<MT, C>(XT, nt, s, lane));
         read_o();
         if constexpr (LATEQ) q_s();
         __builtin_amdgcn_sched_barrier(0);
@@ -1215,8 +1216,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
                         if constexpr (CF::SHARE)
                             xv = xf[j % NNT][s];
                         else
-                            xv = FC::ld(XT + (16 * (x % NNT) + li) * LDC + FC::KF * s +
-                                        (FC::KF / 4) * lg);
+                            xv = FC::ld(frag_piece<MT, C>(XT, x % NNT, s, lane));
                         up[j] = FC::mma(up[j], pf[CF::SHARE ? j / NNT : j][s], xv);
                     }
                 }
@@ -1231,7 +1231,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
 #pragma unroll
                     for (int rr = 0; rr < 4; ++rr)
                         Sacc[j][rr] = fmaf(Sacc[j][rr], gc[p][rr], up[j][rr]);
-                    store4<MT>(SmT + (16 * nt + li) * LDK + 16 * ik + 4 * lg, Sacc[j][0],
+                    store4<MT>(SmT + frag_off<MT, DK>(16 * nt + li, 16 * ik + 4 * lg), Sacc[j][0],
                                Sacc[j][1], Sacc[j][2], Sacc[j][3]);
                 }
             }
