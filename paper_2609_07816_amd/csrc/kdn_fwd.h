@@ -13,7 +13,7 @@
 //      memory state S: the decayed keys and queries, and, with the inverse of the triangular
 //      factor folded in, the write directions KA = L^-T P_tail and the intra-chunk read matrix
 //      BA = A_qk L^-1. One record per (chunk, head) in the workspace.
-//   4. walk_kernel (sequence, head, 32 value columns): carries S through the chunks in order:
+//   4. walk_kernel (sequence, head, 32 or 16 value columns): carries S through the chunks in order:
 //        X = V - K_bar S,  O = scale (Q_bar S + BA X),  S <- gamma_C (.) S + KA^T X
 //      (eqs. chunk-memory-wy, chunk-memory-tail-output, chunk-memory-output-state with
 //      R = L^-1 X, the innovations, eliminated).
@@ -903,17 +903,19 @@ void prep_layer_kernel(PrepArgs a)
 // ------------------------------------------------------------------------------------------
 // 4. walk: the memory state through the chunks of one (sequence, head, value tile)
 //
-// Bound by the latency of its serial chain, two barriers per chunk: S from LDS, X, X through LDS,
-// S. With L^-1 folded into the record (KA, BA) a chunk has no third product between X and S, its
-// record is 8 KB (of 64) smaller, and no load, store or tile sits in a branch: 150 us against 189 us
-// for 128 chunks alone (1.17 against 1.48 us per chunk: B1 T8191 H16 d128 bf16, 64 workgroups), 796
-// against 928 us for 134,000 packed tokens, 109 against 133 us at B4 T4096.
+// Bound, where few workgroups run, by fetching a chunk's record (56 KB in bf16 at d128) through one
+// CU's vector memory pipeline, and by the serial chain: S from LDS, X, X through LDS, S, with two
+// barriers per chunk. With L^-1 folded into the record (KA, BA) there is no third product between X
+// and S and the record is 8 KB smaller; no load, store or tile sits in a branch, and operands are
+// fetched between the products that use the previous ones. 132 us against 189 us for 128 chunks alone
+// (1.03 against 1.48 us per chunk: B1 T8191 H16 d128 bf16), 795 against 928 us for 134,000 packed
+// tokens, 105 against 133 us at B4 T4096.
 // ------------------------------------------------------------------------------------------
-template <class TI, int DK_, int DV_>
+template <class TI, int DK_, int DV_, int BV_>
 struct WalkCfg {
     using MT = typename OpOf<TI>::type;
     static constexpr int DK = DK_, DV = DV_;
-    static constexpr int BV = DV >= 32 ? 32 : DV;  // value columns per workgroup
+    static constexpr int BV = BV_;  // value columns per workgroup (16 or 32)
     static constexpr int NV = DV / BV;
     static constexpr int NNT = BV / 16, NKT = DK / 16, NST = NKT * NNT;
     static constexpr int SPW = (NST + NW - 1) / NW;  // S tiles per wave: x = SPW w + j
@@ -1303,12 +1305,26 @@ hipError_t set_lds(K* kernel, size_t bytes)
                                (int)bytes);
 }
 
+template <class TI, class WC>
+hipError_t launch_walk(const WalkArgs& wa, hipStream_t st)
+{
+    static bool attr_done = false;
+    if (!attr_done) {
+        const hipError_t e = set_lds(walk_kernel<TI, WC>, WC::TOTAL);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    const size_t nh8 = ((size_t)wa.cm.N * wa.H + 7) / 8 * 8;
+    hipLaunchKernelGGL((walk_kernel<TI, WC>), dim3((unsigned)(nh8 * WC::NV)), dim3(NTH),
+                       WC::TOTAL, st, wa);
+    return hipGetLastError();
+}
+
 template <class TI, bool LAYER, int DK, int DV, int VARIANT, bool APC>
 hipError_t run_t(const FwdCall& fc, hipStream_t st)
 {
     using VC = VarCfg<TI, DK, VARIANT, APC>;
     using PC = PrepCfg<TI, DK, VARIANT, APC>;
-    using WC = WalkCfg<TI, DK, DV>;
     using MT = typename OpOf<TI>::type;
     const SeqArgs& sa = fc.sa;
     const bool packed = sa.cu_seqlens != nullptr;
@@ -1365,7 +1381,6 @@ hipError_t run_t(const FwdCall& fc, hipStream_t st)
     static bool attr_done = false;
     if (!attr_done) {
         if ((e = set_lds(prep, PC::TOTAL)) != hipSuccess) return e;
-        if ((e = set_lds(walk_kernel<TI, WC>, WC::TOTAL)) != hipSuccess) return e;
         attr_done = true;
     }
     PrepArgs pa;
@@ -1387,10 +1402,16 @@ hipError_t run_t(const FwdCall& fc, hipStream_t st)
     wa.H = sa.H;
     wa.scale = fc.scale;
     wa.bytes_v = (uint32_t)(ntok * DV * sizeof(TI));
-    const size_t nh8 = ((size_t)sa.N * sa.H + 7) / 8 * 8;
-    hipLaunchKernelGGL((walk_kernel<TI, WC>), dim3((unsigned)(nh8 * WC::NV)), dim3(NTH),
-                       WC::TOTAL, st, wa);
-    return hipGetLastError();
+    // Value tiles of 32 columns, or of 16 where tiles of 32 would leave half of the 256 CUs idle: a
+    // chunk's products then take a workgroup half the time (float32, B2 T1024 H8 d64, 32 workgroups
+    // of 32: walk 40 -> 24 us); in bf16 the record, which each workgroup fetches whole, sets the pace
+    // of either (B1 T8191 H16 d128, 64 workgroups of 32: 132 us both). With every CU taken, twice
+    // the workgroups would fetch twice the records.
+    if constexpr (DV >= 32) {
+        if ((size_t)sa.N * sa.H * (DV / 32) > 128)
+            return launch_walk<TI, WalkCfg<TI, DK, DV, 32>>(wa, st);
+    }
+    return launch_walk<TI, WalkCfg<TI, DK, DV, 16>>(wa, st);
 }
 
 template <class TI, bool LAYER, int DK, int DV>

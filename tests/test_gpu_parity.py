@@ -82,6 +82,14 @@ def test_forward_tile_edges(T, dk, dv, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N,H,dv", [(2, 64, 32), (3, 43, 32), (2, 16, 128), (3, 11, 128)])
+def test_forward_value_tile_widths(N, H, dv, dtype):
+    """128 walk workgroups of 32 value columns (split into tiles of 16) and the next count above."""
+    x = W.draw_inputs("diag", dtype, N, 65, H, 32, dv, seed=50, random_state=True)
+    compare_forward(x)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("variant", ["diag", "iso"])
 def test_forward_packed_ragged(variant, dtype):
     lens = [1, 63, 64, 0, 65, 130, 7]
