@@ -117,24 +117,46 @@ def _check(status: int, where: str):
                                       f"{L.kdn_last_error().decode()}")
 
 
+# Pointers, sizes and floats go to the library as plain Python numbers, which its argument types
+# convert; a ctypes object made for each of them first would double the cost of a call.
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     if not t.is_contiguous():
         raise ValueError("tensors passed to libkdn must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _ptrs(*ts):
+    """_ptr of each tensor, in one call."""
+    out = []
+    for t in ts:
+        if t is None:
+            out.append(None)
+        elif t.is_contiguous():
+            out.append(t.data_ptr())
+        else:
+            raise ValueError("tensors passed to libkdn must be contiguous")
+    return out
+
+
+_DTYPE_CODES = {torch.float32: KDN_F32, torch.bfloat16: KDN_BF16}
 
 
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return KDN_F32
-    if t.dtype == torch.bfloat16:
-        return KDN_BF16
-    raise TypeError(f"unsupported input dtype {t.dtype} (float32 or bfloat16)")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported input dtype {t.dtype} (float32 or bfloat16)")
+    return code
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    # the raw handle of the device's current stream (torch.cuda.current_stream makes a Stream object
+    # of it first); it also raises for a device that is not a GPU
+    index = device.index
+    if index is not None and device.type == "cuda":
+        return torch._C._cuda_getCurrentRawStream(index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _same(dtype, *ts):
@@ -169,7 +191,7 @@ def _forward(variant, q, k, v, alpha, omega, r, S0, P0, cu_seqlens, mu, scale, c
     common = [_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega), _ptr(r), _ptr(_f32(S0)),
               _ptr(_f32(P0)), _ptr(o), _ptr(S_T), _ptr(P_T), _ptr(cu), N, B, T, H, dk, dv,
               _dtype_code(k)]
-    tail = [ctypes.c_float(mu), ctypes.c_float(scale), int(chunk), _ptr(ws),
+    tail = [mu, scale, int(chunk), _ptr(ws),
             ws_bytes, _stream(dev)]
     if variant == 0:
         st = lib().kdn_forward_diag(*common, *tail)
@@ -207,7 +229,7 @@ def forward_diag_noalloc(q, k, v, alpha, omega, r, S0=None, P0=None, cu_seqlens=
     st = lib().kdn_forward_diag_noalloc(
         _ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega), _ptr(r), _ptr(_f32(S0)),
         _ptr(_f32(P0)), _ptr(o), _ptr(_f32(S_T)), _ptr(_f32(P_T)), _ptr(cu_seqlens), N, B, T, H,
-        dk, dv, _dtype_code(k), ctypes.c_float(mu), ctypes.c_float(scale), _stream(dev))
+        dk, dv, _dtype_code(k), mu, scale, _stream(dev))
     _check(st, "kdn_forward_diag_noalloc")
     return o, S_T, P_T
 
@@ -232,11 +254,11 @@ def decode_step(variant, q, k, v, alpha, omega, r, S, P, slot_idx=None, mu=None,
     mu = float(dk if mu is None else mu)
     scale = float(dk ** -0.5 if scale is None else scale)
     apc = int(alpha.dim() == 3)
-    st = lib().kdn_decode_step(vid, _ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega), _ptr(r),
-                               _ptr(_f32(S)), _ptr(_f32(P)), _ptr(slot_idx), _ptr(o), R,
-                               S.shape[0], H, dk, dv, _dtype_code(k), apc, ctypes.c_float(mu),
-                               ctypes.c_float(scale), _stream(k.device))
-    _check(st, "kdn_decode_step")
+    ptrs = _ptrs(q, k, v, alpha, omega, r, _f32(S), _f32(P), slot_idx, o)
+    st = lib().kdn_decode_step(vid, *ptrs, R, S.shape[0], H, dk, dv, _dtype_code(k), apc, mu, scale,
+                               _stream(k.device))
+    if st != KDN_OK:
+        _check(st, "kdn_decode_step")
     return o
 
 
@@ -255,11 +277,11 @@ def _gain(variant, k, alpha, omega, r, P0, cu_seqlens, mu, want_phat):
     args = [_ptr(k), _ptr(alpha), _ptr(omega), _ptr(r), _ptr(_f32(P0)), _ptr(gain), _ptr(phat),
             _ptr(P_T), _ptr(cu_seqlens), N, B, T, H, dk, _dtype_code(k)]
     if variant == 0:
-        st = lib().kdn_gain_diag(*args, ctypes.c_float(mu), _ptr(ws), ws_bytes, _stream(dev))
+        st = lib().kdn_gain_diag(*args, mu, _ptr(ws), ws_bytes, _stream(dev))
         _check(st, "kdn_gain_diag")
     else:
         apc = int(alpha.dim() == 4)
-        st = lib().kdn_gain_iso(*args, apc, ctypes.c_float(mu), _ptr(ws), ws_bytes, _stream(dev))
+        st = lib().kdn_gain_iso(*args, apc, mu, _ptr(ws), ws_bytes, _stream(dev))
         _check(st, "kdn_gain_iso")
     return gain, phat, P_T
 
@@ -309,7 +331,7 @@ def forward_layer(variant, q, k, v, alpha, omega, r, S0=None, P0=None, cu_seqlen
     st = lib().kdn_forward_layer(vid, _ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega),
                                  _ptr(r), _ptr(_f32(S0)), _ptr(_f32(P0)), _ptr(o), _ptr(S_T),
                                  _ptr(P_T), _ptr(cu_seqlens), N, B, T, H, dk, dv, _dtype_code(k),
-                                 apc, ctypes.c_float(mu), ctypes.c_float(scale),
+                                 apc, mu, scale,
                                  ctypes.byref(opts), _ptr(ws), ws_bytes, _stream(dev))
     _check(st, "kdn_forward_layer")
     return o, S_T, P_T, beff
@@ -336,12 +358,11 @@ def decode_step_layer(variant, q, k, v, alpha, omega, r, S, P, slot_idx=None, mu
     scale = float(dk ** -0.5 if scale is None else scale)
     apc = int(alpha.dim() == 3)
     opts = _layer_opts(gates_preact, r_min, qk_l2norm, mu_t, beta_eff)
-    st = lib().kdn_decode_step_layer(vid, _ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega),
-                                     _ptr(r), _ptr(_f32(S)), _ptr(_f32(P)), _ptr(slot_idx),
-                                     _ptr(o), R, S.shape[0], H, dk, dv, _dtype_code(k), apc,
-                                     ctypes.c_float(mu), ctypes.c_float(scale),
-                                     ctypes.byref(opts), _stream(k.device))
-    _check(st, "kdn_decode_step_layer")
+    ptrs = _ptrs(q, k, v, alpha, omega, r, _f32(S), _f32(P), slot_idx, o)
+    st = lib().kdn_decode_step_layer(vid, *ptrs, R, S.shape[0], H, dk, dv, _dtype_code(k), apc, mu,
+                                     scale, opts, _stream(k.device))
+    if st != KDN_OK:
+        _check(st, "kdn_decode_step_layer")
     return o
 
 
@@ -372,7 +393,7 @@ def backward(variant, q, k, v, alpha, omega, r, S0=None, P0=None, cu_seqlens=Non
     apc = int(vid == 0 or alpha.dim() == 4)
     st = lib().kdn_backward(vid, _ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega), _ptr(r),
                             _ptr(_f32(S0)), _ptr(_f32(P0)), _ptr(cu_seqlens), N, B, T, H, dk, dv,
-                            _dtype_code(k), apc, ctypes.c_float(mu), ctypes.c_float(scale),
+                            _dtype_code(k), apc, mu, scale,
                             _ptr(dO), _ptr(_f32(dS_T)), _ptr(_f32(dP_T)), _ptr(g["dq"]),
                             _ptr(g["dk"]), _ptr(g["dv"]), _ptr(g["dalpha"]), _ptr(g["domega"]),
                             _ptr(g["dr"]), _ptr(g["dS0"]), _ptr(g["dP0"]), _ptr(ws), ws_bytes,
@@ -397,6 +418,6 @@ def forward_kam(q, k, v, alpha, omega, r, S0=None, P0=None, cu_seqlens=None, sca
     st = lib().kdn_forward_kam(_ptr(q), _ptr(k), _ptr(v), _ptr(alpha), _ptr(omega), _ptr(r),
                                _ptr(_f32(S0)), _ptr(_f32(P0)), _ptr(o), _ptr(S_T), _ptr(P_T),
                                _ptr(cu_seqlens), N, B, T, H, dk, dv, _dtype_code(k),
-                               ctypes.c_float(scale), _stream(dev))
+                               scale, _stream(dev))
     _check(st, "kdn_forward_kam")
     return o, S_T, P_T
