@@ -3,7 +3,7 @@
 // then the chunkwise memory scan.
 //
 // Tokens are cut into chunks of C = 64 (restarting at every sequence start; the last chunk of a
-// sequence may be partial). Four kernels per call:
+// sequence may be partial). Four kernels per call (short sequences: kernel 3 does kernel 2's work):
 //   1. summary_kernel (chunk, head): the product of each chunk's 2x2 Moebius token matrices per
 //      key channel (diagonal) or per head (isotropic)               eq. chunk-gain-summary
 //   2. carry_scan_kernel (sequence, head, channel): the variance state entering every chunk, a
@@ -421,10 +421,21 @@ struct PrepCfg : VarCfg<TI, DK_, VARIANT_, APC_> {
 struct PrepArgs {
     InArgs in;
     ChunkMap cm;
-    const float2* carry;  // [maxch][H][nchan]
+    const float2* carry;  // [maxch][H][nchan], or nullptr: compose it from summ and P0
+    const float4* summ;   // [maxch][H][nchan] (read when carry is nullptr, past a first chunk)
+    const float* P0;
     char* ops;            // [maxch][H] records
     float* P_T;
 };
+
+// The variance state entering chunk m of a sequence, composed in order from the summaries of the
+// chunks before it (at `summ`, `stride` apart), where no scan has stored it.
+__device__ __forceinline__ float2 compose_carry(const float4* summ, size_t stride, int m, float p0)
+{
+    float2 z = make_float2(p0, 1.f);
+    for (int i = 0; i < m; ++i) z = mat_vec(summ[(size_t)i * stride], z);
+    return z;
+}
 
 // One block pair (ib, jb) of M and M^q from LDS operand tiles; the column side optionally
 // scaled per channel by rho.
@@ -554,8 +565,19 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
     float2 Gs = make_float2(1.f, 1.f), Gt = make_float2(1.f, 1.f);
     {
         const size_t cidx = ((size_t)g * H + h) * CF::NCHAN;
+        const size_t cstr = (size_t)H * CF::NCHAN;
+        const int m = g - n * ((a.cm.T + C - 1) / C);  // with no stored carry: the chunk's index
         if constexpr (DIAG) {
-            float2 z0 = a.carry[cidx + ch], z1 = a.carry[cidx + ch + 1];
+            float2 z0, z1;
+            if (a.carry) {
+                z0 = a.carry[cidx + ch];
+                z1 = a.carry[cidx + ch + 1];
+            } else {
+                const float* p0 = a.P0 ? a.P0 + (size_t)nh * DK + ch : nullptr;
+                const float4* s0 = a.summ + (cidx - m * cstr) + ch;
+                z0 = compose_carry(s0, cstr, m, p0 ? p0[0] : 1.f);
+                z1 = compose_carry(s0 + 1, cstr, m, p0 ? p0[1] : 1.f);
+            }
 #pragma unroll
             for (int b = 0; b < NB - 1; ++b)
                 if (b < w) {
@@ -564,7 +586,9 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
                 }
             n0 = z0.x; d0 = z0.y; n1 = z1.x; d1 = z1.y;
         } else {
-            float2 z = a.carry[cidx];
+            float2 z = a.carry ? a.carry[cidx]
+                               : compose_carry(a.summ + (cidx - m * cstr), cstr, m,
+                                               a.P0 ? a.P0[nh] : 1.f);
 #pragma unroll
             for (int b = 0; b < NB - 1; ++b)
                 if (b < w) z = mat_vec(segA[b * DK], z);
@@ -886,7 +910,9 @@ __device__ __forceinline__ void prep_body(const PrepArgs& a)
 }
 
 template <class TI, class CF>
-__global__ __launch_bounds__(NTH) void prep_kernel(PrepArgs a)
+__global__ __launch_bounds__(NTH)
+__attribute__((amdgpu_waves_per_eu(sizeof(TI) == 2 || CF::DK <= 64 ? 2 : 1)))
+void prep_kernel(PrepArgs a)
 {
     prep_body<TI, CF, false>(a);
 }
@@ -1366,13 +1392,25 @@ hipError_t run_t(const FwdCall& fc, hipStream_t st)
     float4* summ = (float4*)(ws + wm.summ);
     float2* carry = (float2*)(ws + wm.carry);
     const dim3 cgrid((unsigned)((size_t)wm.maxch * sa.H));
-    if constexpr (LAYER)
-        hipLaunchKernelGGL((summary_layer_kernel<TI, VC>), cgrid, dim3(NTH), 0, st, in, cm, summ);
-    else
-        hipLaunchKernelGGL((summary_kernel<TI, VC>), cgrid, dim3(NTH), 0, st, in, cm, summ);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = launch_carry_scan(summ, fc.P0, cm, C, sa.H, VC::NCHAN, carry, fc.P_T, st)) !=
-        hipSuccess)
+    // Sequences of equal lengths of at most two chunks, or of at most eight in up to 1024 workgroups:
+    // prep composes its carry from the summaries before it, and the scan is not launched (nor, for
+    // single chunks, the summaries): B1 H16 d128 bf16 diagonal, T64 20.0 -> 14.5 us, T128 20.8 -> 18.5,
+    // T512 26.2 -> 24.7; B256 T64 501 -> 300, B128 T128 381 -> 316. Past that the re-read summaries
+    // cost more than the scan: T1024 34.0 and 35.6 us, B64 T512 567 and 577. Not where P_T is P0
+    // itself: another workgroup of prep may have written it already.
+    const int nch = (sa.T + C - 1) / C;
+    const bool compose = !packed && (nch <= 2 || (nch <= 8 && cgrid.x <= 1024)) &&
+                         !(fc.P0 && fc.P0 == fc.P_T);
+    if (!(compose && nch == 1)) {
+        if constexpr (LAYER)
+            hipLaunchKernelGGL((summary_layer_kernel<TI, VC>), cgrid, dim3(NTH), 0, st, in, cm,
+                               summ);
+        else
+            hipLaunchKernelGGL((summary_kernel<TI, VC>), cgrid, dim3(NTH), 0, st, in, cm, summ);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (!compose && (e = launch_carry_scan(summ, fc.P0, cm, C, sa.H, VC::NCHAN, carry, fc.P_T,
+                                           st)) != hipSuccess)
         return e;
     void (*prep)(PrepArgs) = [] {
         if constexpr (LAYER) return &prep_layer_kernel<TI, PC>;
@@ -1386,7 +1424,9 @@ hipError_t run_t(const FwdCall& fc, hipStream_t st)
     PrepArgs pa;
     pa.in = in;
     pa.cm = cm;
-    pa.carry = carry;
+    pa.carry = compose ? nullptr : carry;
+    pa.summ = summ;
+    pa.P0 = fc.P0;
     pa.ops = ws + wm.ops;
     pa.P_T = fc.P_T;
     hipLaunchKernelGGL(prep, cgrid, dim3(NTH), PC::TOTAL, st, pa);

@@ -89,6 +89,32 @@ def test_forward_value_tile_widths(N, H, dv, dtype):
     compare_forward(x)
 
 
+@pytest.mark.parametrize("variant,apc", [("diag", True), ("iso", True), ("iso", False)])
+@pytest.mark.parametrize("N,T,H", [(2, 64, 2), (2, 512, 2), (2, 513, 2), (2, 512, 64),
+                                   (2, 449, 65), (2, 128, 260)])
+def test_forward_composed_carry(variant, apc, N, T, H):
+    """Variance carries composed inside the operand kernel (one chunk; up to eight chunks and 1024
+    chunk-heads; two chunks of any number of heads) and the next sizes, which take the scan."""
+    x = W.draw_inputs(variant, "f32", N, T, H, 16, 16, seed=51, alpha_per_channel=apc,
+                      random_state=True)
+    compare_forward(x)
+
+
+@pytest.mark.parametrize("T", [40, 500])
+def test_forward_states_in_place(T):
+    """S_T and P_T are S0 and P0 themselves: the same values as with separate outputs."""
+    x = W.draw_inputs("diag", "f32", 2, T, 2, 32, 32, seed=52, random_state=True)
+    from paper_2609_07816_amd import kdn
+    d = to_device(x)
+    S, P = d["S0"], d["P0"]
+    o, S_T, P_T = kdn.forward_diag_noalloc(*(d[n] for n in NAMES), S0=S, P0=P, S_T=S, P_T=P,
+                                           mu=x.mu, scale=x.scale)
+    assert S_T is S and P_T is P
+    ref = run_oracle_forward(x)
+    for name, got in (("o", o), ("S_T", S), ("P_T", P)):
+        check(name, host_f64(got), ref[name], TOL["f32"])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("variant", ["diag", "iso"])
 def test_forward_packed_ragged(variant, dtype):
