@@ -6,8 +6,8 @@
 // sequence may be partial). Four kernels per call (short sequences: kernel 3 does kernel 2's work):
 //   1. summary_kernel (chunk, head): the product of each chunk's 2x2 Moebius token matrices per
 //      key channel (diagonal) or per head (isotropic)               eq. chunk-gain-summary
-//   2. carry_scan_kernel (sequence, head, channel): the variance state entering every chunk, a
-//      log-depth scan of the summaries                               eq. chunk-gain-carry
+//   2. the carry scan (sequence, head, channel): the variance state entering every chunk, a
+//      parallel scan of the summaries                                eq. chunk-gain-carry
 //   3. prep_kernel (chunk, head): replays the chunk from its carry (eqs. chunk-gain-local-prefix,
 //      chunk-gain-emission) and builds everything of the memory scan that does not depend on the
 //      memory state S: the decayed keys and queries, and, with the inverse of the triangular

@@ -100,6 +100,17 @@ def test_forward_composed_carry(variant, apc, N, T, H):
     compare_forward(x)
 
 
+@pytest.mark.parametrize("nch", [12, 15, 17, 64, 65])
+def test_forward_carry_scan_segments(nch):
+    """Chunk counts around the carry scan's segments (four chunks each, 16 in a step), with a packed
+    batch that mixes them."""
+    x = W.draw_inputs("diag", "f32", 1, 64 * nch - 7, 1, 16, 16, seed=53, random_state=True)
+    compare_forward(x)
+    lens = [64 * nch, 0, 33, 64 * 17 + 1]
+    compare_forward(W.draw_inputs("diag", "f32", 1, sum(lens), 1, 16, 16, seed=54, lengths=lens,
+                                  random_state=True))
+
+
 @pytest.mark.parametrize("T", [40, 500])
 def test_forward_states_in_place(T):
     """S_T and P_T are S0 and P0 themselves: the same values as with separate outputs."""
