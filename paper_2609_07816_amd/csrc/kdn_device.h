@@ -334,7 +334,7 @@ __device__ __forceinline__ bool locate_chunk(const ChunkMap& cm, int g, int& n, 
 hipError_t launch_chunk_table(const int32_t* cu, int N, int ntok, int ch, int maxch,
                               int32_t* choff, hipStream_t st);
 // Exclusive carries of the variance chain across the chunks of every (sequence, head, channel)
-// as a log-depth (Kogge-Stone) scan of the chunk summaries summ [maxch][H][nchan]; carry has the
+// as a log-depth scan of the chunk summaries summ [maxch][H][nchan]; carry has the
 // same layout. Empty sequences get P_T = P0 (P_T may be NULL).
 hipError_t launch_carry_scan(const float4* summ, const float* P0, const ChunkMap& cm, int ch,
                              int H, int nchan, float2* carry, float* P_T, hipStream_t st);

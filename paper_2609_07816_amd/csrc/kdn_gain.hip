@@ -8,7 +8,7 @@
 // w = omega, u = mu ||k||^2 / (dk r) for the isotropic head (eqs. diag-cov-scan,
 // iso-kla-box-mobius). Three passes:
 //   1. chunk summaries  M_bar_m = M_r ... M_l                      (eq. chunk-gain-summary)
-//   2. exclusive carries z_in_m = M_bar_{m-1} ... M_bar_0 z_0, as a Kogge-Stone scan across
+//   2. exclusive carries z_in_m = M_bar_{m-1} ... M_bar_0 z_0, as a scan across
 //      the chunks of a sequence (log depth; eq. chunk-gain-carry)
 //   3. replay of every chunk from its carry, emitting p_hat and the gain before each token's
 //      matrix is applied (eqs. chunk-gain-local-prefix, chunk-gain-emission).

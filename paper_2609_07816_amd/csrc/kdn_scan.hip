@@ -8,7 +8,7 @@
 //   z_in_m = M_bar_{m-1} ... M_bar_0 z_0,   z_0 = [p_0; 1],
 // an exclusive scan with an associative operator, 64 chunks per step (longer sequences carry step
 // to step): one variance per head (isotropic) as a Kogge-Stone scan inside one wavefront, log2(64) =
-// 6 rounds; one per channel (diagonal) in segments.
+// 6 rounds; one per channel (diagonal) as a tree of products of four.
 #include "kdn_device.h"
 
 namespace kdn {
@@ -33,22 +33,24 @@ __device__ __forceinline__ float4 shfl_up4(float4 x, int off)
                        __shfl_up(x.z, off, 64), __shfl_up(x.w, off, 64));
 }
 
-// Diagonal: 16 channels per workgroup, in 16 segments of SEGC chunks each (64 chunks per step).
-// A thread loads its segment's summaries at once (a row of 16 channels is 256 contiguous bytes),
-// multiplies them, applies the segments before its own to the state, and replays its chunks. Bound
-// by the latency of one load and of the 15 products between segments. A wavefront per channel with
-// a lane per chunk (16-byte reads H d_k apart, 6 shuffle rounds) took 51 us for 2,100 chunks of 32
-// packed sequences (16 heads, d128) against 22 us, and 6.0 against 5.6 us for 4 x 64 chunks;
-// prefixes of the segments by shuffles in place of the 15 products, 53 and 7.8 us.
+// Diagonal: 16 channels per workgroup, a tree of three levels over 64 chunks per step: four chunks in
+// each of 16 segments (a thread's loads, a row of 16 channels being 256 contiguous bytes), four
+// segments in each wavefront, four wavefronts. A thread applies the wavefronts before its own, the
+// segments before its own, and replays its chunks. Bound by the latency of one load and of that
+// chain. A wavefront per channel with a lane per chunk (16-byte reads H d_k apart, 6 shuffle rounds)
+// took 51 us for 2,100 chunks of 32 packed sequences (16 heads, d128) against 21 us, and 6.0 against
+// 5.5 us for 4 x 64 chunks; two levels, 16 segments in order, 22 and 5.6 us.
 constexpr int CPB = 16, NSEG = 16, SEGC = 4;
 __global__ __launch_bounds__(CPB * NSEG) void carry_scan_diag_kernel(
     const float4* __restrict__ summ, const float* __restrict__ P0, ChunkMap cm, int ch, int H,
     int nchan, float2* __restrict__ carry, float* __restrict__ P_T)
 {
-    __shared__ float4 seg[NSEG][CPB];
+    constexpr int NWV = CPB * NSEG / 64, SPW = 64 / CPB;  // wavefronts, segments in each
+    __shared__ float4 seg[NSEG][CPB], s_wave[NWV][CPB];
     __shared__ float2 s_in[CPB];
     const int n = blockIdx.x / H, h = blockIdx.x % H;
     const int cl = threadIdx.x % CPB, sg = threadIdx.x / CPB;
+    const int w = sg / SPW, sw = sg % SPW;  // wavefront, segment within it
     const int c = CPB * blockIdx.y + cl;
     int t0, t1;
     seq_span(cm, n, t0, t1);
@@ -63,7 +65,6 @@ __global__ __launch_bounds__(CPB * NSEG) void carry_scan_diag_kernel(
     const size_t base = ((size_t)g0 * H + h) * nchan + c, stride = (size_t)H * nchan;
     float2 zin = make_float2(P0 ? P0[pidx] : 1.f, 1.f);  // z_0 = [p_0; 1]
     for (int b0 = 0; b0 < nch; b0 += NSEG * SEGC) {
-        const int nseg = min(NSEG, (nch - b0 + SEGC - 1) / SEGC);  // segments with chunks
         const int m0 = b0 + SEGC * sg;
         float4 x[SEGC];
 #pragma unroll
@@ -76,12 +77,22 @@ __global__ __launch_bounds__(CPB * NSEG) void carry_scan_diag_kernel(
         for (int i = 1; i < SEGC; ++i) p = mat_mul(x[i], p);
         seg[sg][cl] = p;
         __syncthreads();
+        if (sw == 0) {  // the product of the wavefront's segments
+#pragma unroll
+            for (int q = 1; q < SPW; ++q) p = mat_mul(seg[sg + q][cl], p);
+            s_wave[w][cl] = p;
+        }
+        __syncthreads();
         float2 z = zin;
 #pragma unroll
-        for (int q = 0; q < NSEG - 1; ++q) {
-            if (q >= nseg - 1) break;
-            const float2 y = mat_vec(seg[q][cl], z);
-            z = q < sg ? y : z;
+        for (int q = 0; q < NWV - 1; ++q) {
+            const float2 y = mat_vec(s_wave[q][cl], z);
+            z = q < w ? y : z;
+        }
+#pragma unroll
+        for (int q = 0; q < SPW - 1; ++q) {
+            const float2 y = mat_vec(seg[SPW * w + q][cl], z);
+            z = q < sw ? y : z;
         }
 #pragma unroll
         for (int i = 0; i < SEGC; ++i) {
