@@ -699,7 +699,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 // issued and waits for the newest loads instead of the oldest. Each operand is fetched again right
 // after the step that used it, between the MFMAs: issued in one burst before the barrier, the four
 // waves' loads queue for the CU's one memory pipeline while no MFMA runs. At B4 T4096 H16 d128
-// (one workgroup per CU, 64 chunks in series): 210 and 312 us, against 272 and 393 us with bursts
+// (one workgroup per CU, 64 chunks in series): 206 and 306 us, against 272 and 393 us with bursts
 // and a product's dependent steps in sequence, and 589 and 721 us with the operands staged through
 // LDS and L^-1 applied inside the walk (a third product and barrier per chunk).
 // ------------------------------------------------------------------------------------------
@@ -1112,7 +1112,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
 // The log-decay adjoint of an entry is then q dq + k dk - kappa dkappa; its chunk-end part enters
 // through column sums.
 // 79 KB of LDS and 256 registers: two workgroups per CU, so that one's loads, barriers and scalar
-// phases run under the other's MFMAs. B4 T4096 H16 d128: 712 us against 1222 us with LDS slabs of
+// phases run under the other's MFMAs. B4 T4096 H16 d128: 704 us against 1222 us with LDS slabs of
 // the state and exponentials of float64 log-decays; eight waves with every channel staged at once
 // (156 KB, one workgroup per CU) took 1013 us. Its float32 MFMAs take 300 us, its 1.6 GB 340 us.
 template <int DK>
