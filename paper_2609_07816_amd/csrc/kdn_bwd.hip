@@ -528,7 +528,9 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
             lb[row * LDL + li] = row > li ? t[rr] : (row == li ? cd : 0.f);
         }
     }
+    wave_lds_fence();
     if (vact) put_mid(X0, Qf, false);
+    wave_lds_fence();
     floatx4 aqd = op_prod<NKT>(X0, X1, w, w, nullptr, nullptr, li, lg);
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) aqd[rr] = 4 * lg + rr >= li ? aqd[rr] : 0.f;
@@ -536,6 +538,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
     // ---- blocks off the diagonal: rows referenced to their block's start, columns to their
     // block's end, the decay of the blocks between applied to the column side. Pairs per wave:
     // 0: (1,0) (3,0); 1: (2,1) (3,1); 2: (3,2) (2,0); 3: the diagonal blocks of L^-1 ----------
+    wave_lds_fence();
     if (vact) {
         put_start(X0, Kf);
         float2 Q = make_float2(1.f, 1.f);
@@ -582,6 +585,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
             for (int kq = 0; kq < mq; ++kq) sacc[kq] = fmaf(y[mq], cur[kq], sacc[kq]);
         }
+        wave_lds_fence();
 #pragma unroll
         for (int v4 = 0; v4 < 4; ++v4)
             stv(Lb + li * LDL + 4 * v4,
@@ -655,6 +659,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr) p[(4 * lg + rr) * LDL + li] = lt[b][rr];
         }
+    wave_lds_fence();
 #pragma unroll
     for (int b = 0; b < NB; ++b)
         if (b >= w)

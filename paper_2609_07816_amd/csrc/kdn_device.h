@@ -88,6 +88,17 @@ template <int K> struct Frag<float, K> {
     }
 };
 
+// Between a store to LDS and another lane's read of it in the same wavefront (or a read and the
+// store over it) where no barrier stands. The unit runs one wavefront's LDS operations in order, so
+// this is for the compiler alone, which may otherwise reorder a lane's accesses to addresses that it
+// finds distinct. No instruction.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // 16 x 16 x 16 float32 products from register fragments: lane (g, i) holds A[i][4g..4g+3]
 // (A side) or B[4g..4g+3][i] (B side). A result tile (lane (g, i): rows 4g..4g+3 of column i)
 // is therefore already a B fragment of the next product.

@@ -1091,10 +1091,10 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     auto store_v = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < CF::VPW; ++u) {
-            const int q = lane + 64 * u;
-            if (q < 16 * CF::VPC)
-                *reinterpret_cast<uintx4*>(Vt + (16 * w + q / CF::VPC) * LDO +
-                                          (q % CF::VPC) * (16 / es)) = vraw[u];
+            // lanes past the last piece hold it too and store it again: no branch
+            const int q = min(lane + 64 * u, 16 * CF::VPC - 1);
+            *reinterpret_cast<uintx4*>(Vt + (16 * w + q / CF::VPC) * LDO +
+                                       (q % CF::VPC) * (16 / es)) = vraw[u];
         }
     };
     const rsrc_t ro = make_rsrc(a.o, a.bytes_v);
@@ -1160,13 +1160,14 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     for (int m = 0; m < nch; ++m) {
         const int c0 = t0 + m * C;
         // ---- X = V - K_bar S (to LDS, transposed; the record holds -K_bar) ------------------
+        store_v();
+        wave_lds_fence();
         typename FK::V sf[NNT][NSK];
 #pragma unroll
         for (int s = 0; s < NSK; ++s)
 #pragma unroll
             for (int nt = 0; nt < NNT; ++nt)
                 sf[nt][s] = FK::ld(frag_piece<MT, DK>(SmT, nt, s, lane));
-        store_v();
         load_v(m + 1);
         floatx4 vr[NNT];
 #pragma unroll
@@ -1272,6 +1273,7 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     if (nch > 0) {  // the last chunk's O rows
         const int cp = t0 + (nch - 1) * C;
         put_o();
+        wave_lds_fence();
         read_o();
         store_o(cp, t1 - cp);
     }
