@@ -6,12 +6,14 @@
 //  memory scan, given the gains kappa_t = G_t (.) k_t / c_t (G = p_hat and c the gain denominator
 //  for the diagonal variant, G = beta and c = 1 for the isotropic one). Within a chunk of C tokens
 //  with start state S_in and decays gamma_t = prod_{s <= t} alpha_s:
-//      L = diag(c) + tril(M, -1),  M_ts = sum_i k_ti (gamma_t / gamma_s)_i G_si k_si,
-//      A_qk = tril(M^q) (q in place of k, diagonal included),  P_s = (gamma_C / gamma_s) G_s k_s,
-//      X = V - Kbar S_in,  Delta = diag(c) L^-1 X,
+//      L = I + tril(M, -1),  M_ts = sum_i k_ti (gamma_t / gamma_s)_i kappa_si,
+//      A_qk = tril(M^q) (q in place of k, diagonal included),  P_s = (gamma_C / gamma_s) kappa_s,
+//      X = V - Kbar S_in,  Delta = L^-1 X,
 //      O = scale (Qbar S_in + A_qk L^-1 X),  S_out = diag(gamma_C) S_in + KA^T X,  KA = L^-T P,
 //  with Kbar = gamma k, Qbar = gamma q (eqs. chunk-memory-normalization to
-//  chunk-memory-output-state). Its adjoint, with dS_out from the chunk after:
+//  chunk-memory-output-state). The forward leaves the division by c to L's diagonal; here Delta
+//  itself is needed, and c times a row of that inverse has no value where c is infinite (r = inf,
+//  a token without an observation: kappa = 0). Its adjoint, with dS_out from the chunk after:
 //      Psi = dV = (A_qk L^-1)^T scale dO + KA dS_out,
 //      dS_in = diag(gamma_C) dS_out + Qbar^T scale dO - Kbar^T Psi.
 //  L^-1 is folded into KA and A_qk L^-1 once per chunk, so that both walks carry their state with
@@ -247,8 +249,7 @@ struct PrepCfg : fwd::VarCfg<TI, DK_, VARIANT_, APC_> {
     static constexpr size_t OFF_SG = OFF_LF + cmax((size_t)NLT * 16 * LDL * 4, (size_t)NB * DK * 16);
     static constexpr size_t OFF_R = OFF_SG + (size_t)NB * DK * 4;
     static constexpr size_t OFF_MR = OFF_R + (size_t)C * 4;
-    static constexpr size_t OFF_DEN = OFF_MR + (size_t)C * 4;
-    static constexpr size_t TOTAL = al16(OFF_DEN + (size_t)C * 4);
+    static constexpr size_t TOTAL = al16(OFF_MR + (size_t)C * 4);
 };
 
 // Operand tile [C][DK] in LDS, pieces of four channels of one token in MFMA operand order:
@@ -300,7 +301,6 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
     float* segG = (float*)(smem + CF::OFF_SG);
     float* s_r = (float*)(smem + CF::OFF_R);
     float* s_mr = (float*)(smem + CF::OFF_MR);
-    float* s_den = (float*)(smem + CF::OFF_DEN);
 
     const int H = a.H;
     const int g = (int)(blockIdx.x / H), h = (int)(blockIdx.x % H);
@@ -406,8 +406,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
         if (w == 0 && vact) *reinterpret_cast<float2*>(rec + R::GC + ch) = gc;
     }
 
-    // ---- replay (eqs. chunk-gain-local-prefix, chunk-gain-emission): G_t k_t per channel of the
-    // pair, G = p_hat (diagonal) or beta (isotropic); the gain denominators ------------------
+    // ---- replay (eqs. chunk-gain-local-prefix, chunk-gain-emission): kappa_t per channel of the
+    // pair; the gain denominators --------------------------------------------------------------
     // tiles by columns: a channel's four tokens 4 e .. + 3 of block w, its neighbour's beside them
     auto col_piece = [&](float* base, int e) {
         return base + ((size_t)(w * NKT + (ch >> 4)) * 64 + 16 * e + (ch & 15)) * 4;
@@ -433,11 +433,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
                 }
                 pk[j] = make_float2(ph0 * Kf[j].x, ph1 * Kf[j].y);
                 const float z = wave_sum(vact ? fmaf(pk[j].x, Kf[j].x, pk[j].y * Kf[j].y) : 0.f);
-                if (lane == 0) {
-                    const float dn = s_r[t] + z;
-                    s_den[t] = dn;
-                    rec[R::DEN + t] = dn;
-                }
+                const float dn = s_r[t] + z, idn = __builtin_amdgcn_rcpf(dn);
+                if (lane == 0) rec[R::DEN + t] = dn;
+                pk[j].x *= idn;
+                pk[j].y *= idn;
                 d0 = fmaf(Kf[j].x * Kf[j].x * mr, nn0, d0);
                 d1 = fmaf(Kf[j].y * Kf[j].y * mr, nn1, d1);
                 n0 = nn0;
@@ -484,7 +483,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 
     // ---- diagonal blocks: operands referenced to the block midpoint (own rows only, so no
     // barrier between their stores and products). F_t = prod_{8 <= j <= t} alpha_j (t >= 8),
-    // 1 / prod_{t < j <= 7} alpha_j (t < 8); K_t F_t and G_s k_s / F_s give the ratio ---------
+    // 1 / prod_{t < j <= 7} alpha_j (t < 8); K_t F_t and kappa_s / F_s give the ratio ---------
     auto put_mid = [&](float* X, const float2* x, bool inv) __attribute__((always_inline)) {
         float2 b = make_float2(1.f, 1.f);
 #pragma unroll
@@ -524,8 +523,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
             const int row = 4 * lg + rr;
-            const float cd = DIAG ? s_den[SL * w + row] : 1.f;
-            lb[row * LDL + li] = row > li ? t[rr] : (row == li ? cd : 0.f);
+            lb[row * LDL + li] = row > li ? t[rr] : (row == li ? 1.f : 0.f);
         }
     }
     wave_lds_fence();
@@ -563,7 +561,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
         put(ib0, jb0, op_prod<NKT>(X0, X1, ib0, jb0, nullptr, nullptr, li, lg));
         put(ib1, jb1, op_prod<NKT>(X0, X1, ib1, jb1, mid0, mid1, li, lg));
     } else {
-        // Row i of A_bb = L_bb^-1 solves a^T L_bb = e_i^T: a_i = 1 / L_ii, and going down the rows
+        // Row i of A_bb = L_bb^-1 solves a^T L_bb = e_i^T: a_i = 1, and going down the rows
         // m = i, i-1, ..., 0 every finished a_m adds a_m L_m,k to the sums of the k < m
         // (right-looking backward substitution). Lane (b, i) takes row i of block b; the wave has
         // read every tile before it stores over them.
@@ -575,13 +573,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
         for (int mq = 15; mq >= 0; --mq) {
             float cur[16];
 #pragma unroll
-            for (int v4 = 0; v4 < (mq + 4) / 4; ++v4) {
+            for (int v4 = 0; v4 < (mq + 3) / 4; ++v4) {
                 const floatx4 q4 = ldv(Lb + mq * LDL + 4 * v4);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) cur[4 * v4 + e] = q4[e];
             }
-            const float ym = ((mq == li ? 1.f : 0.f) - sacc[mq]) * __builtin_amdgcn_rcpf(cur[mq]);
-            y[mq] = mq > li ? 0.f : ym;
+            y[mq] = mq > li ? 0.f : (mq == li ? 1.f : 0.f) - sacc[mq];
 #pragma unroll
             for (int kq = 0; kq < mq; ++kq) sacc[kq] = fmaf(y[mq], cur[kq], sacc[kq]);
         }
@@ -633,7 +630,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
             }
             if (b >= c) stv(s_li + ltile(b, c) * 256 + 4 * lane, lt[b]);
         }
-        if (vact) {  // P_tail = (gamma_C / gamma_s) G_s k_s, by columns
+        if (vact) {  // P_tail = (gamma_C / gamma_s) kappa_s, by columns
             float px[4], py[4];
             float2 Q = Gt;
 #pragma unroll
@@ -1100,7 +1097,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
 // Wave w of 4 owns row block w: dq, dk and dkappa of its 16 x 16 tiles (one per 16 channels) stay
 // in its registers, and the gates, keys and queries of a lane's tokens 4 g .. 4 g + 3 and channel
 // are at once the rows of its results and the operands that the other row blocks contract over.
-//  0. Delta = diag(c) L^-1 X to LDS, wave w the value tiles w, w + 4.
+//  0. Delta = L^-1 X to LDS, wave w the value tiles w, w + 4.
 //  1. products over the value columns: Psi S_in^T, dO S_in^T and Delta dS_out^T on the owned tiles
 //     (state tiles straight from memory: each is fetched again for the next 16 columns as soon as
 //     it is used), dO Delta^T and Psi Delta^T (the adjoints of B and T) on the lower 16 x 16 blocks
@@ -1189,7 +1186,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
     // ---- 0. Delta ------------------------------------------------------------------------------
     {
         const float* xt = a.xt + gh * C * DV + 4 * lane;
-        for (int ks = w; ks < NJ; ks += 4) {  // Delta^T = X^T L^-T diag(c)
+        for (int ks = w; ks < NJ; ks += 4) {  // Delta^T = X^T L^-T
             floatx4 xf[NB];
 #pragma unroll
             for (int sb = 0; sb < NB; ++sb) xf[sb] = ldv(xt + (sb * NJ + ks) * 256);
@@ -1199,8 +1196,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
                 for (int sb = 0; sb <= tb; ++sb)
                     acc += mm(zero4(), xf[sb], ldv(rec + R::LI + ltile(tb, sb) * 256 + 4 * lane));
-                stv(s_D + ((tb * NJ + ks) * 64 + lane) * 4,
-                    DIAG ? acc * rec[R::DEN + 16 * tb + li] : acc);
+                stv(s_D + ((tb * NJ + ks) * 64 + lane) * 4, acc);
             }
         }
     }

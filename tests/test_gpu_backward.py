@@ -148,6 +148,31 @@ def test_backward_small_gates_and_zero_noise():
     compare_backward(x, seed=96)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r", [1e30, 2e38, float("inf")])
+def test_backward_tokens_without_observation(r, dtype):
+    """Tokens of a huge or infinite observation variance write nothing (kappa = 0) and update no
+    variance; the others' gradients are finite and as with 1e30 in float64 (whose own terms are
+    1e-30 of the rest). They stand at a chunk's first, inner and last tokens."""
+    from paper_2609_07816_amd import kdn
+    x = W.draw_inputs("diag", dtype, 2, 150, 2, 64, 64, seed=99, random_state=True)
+    dO, dS, dP = adjoints(x, 99)
+    at = [0, 1, 37, 63, 64, 100, 149]
+    d = to_device(x)
+    d["r"][:, at] = r
+    got = kdn.backward(x.variant, *[d[n] for n in NAMES], S0=d["S0"], P0=d["P0"], mu=x.mu,
+                       scale=x.scale, dO=dev_tensor(dO, dtype), dS_T=torch.from_numpy(dS).cuda(),
+                       dP_T=torch.from_numpy(dP).cuda())
+    torch.cuda.synchronize()
+    ins = {n: x.f64(n) for n in NAMES}
+    ins["r"] = ins["r"].copy()
+    ins["r"][:, at] = 1e30
+    ref = oracle.backward(x.variant, *[ins[n] for n in NAMES], S0=x.S0, P0=x.P0, mu=x.mu,
+                          scale=x.scale, dO=W.to_f64(dO, dtype), dS_T=dS, dP_T=dP)
+    for name in GRADS:
+        check(name, host_f64(got[name]), ref[name])
+
+
 # ---------------------------------------------------------------------------------------------
 # full-size workloads (the isotropic B4 T2048 and the diagonal B4 T4096 at H16 d128, bf16), the
 # backward run once over the whole batch, checked on sampled (batch row, head) chains: each
