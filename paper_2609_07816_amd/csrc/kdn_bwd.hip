@@ -1034,7 +1034,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
             for (int i = 0; i < CF::NP; ++i) load_a(m - 1, s + i);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // the tiles tb < w are zero (wave 0 has all four); two partial sums
+        // the tiles tb < w are zero (wave 0 has all four): zeros times the wave's own rows of dO, so
+        // that a value that is not finite in an earlier row stays out of this block; two partial sums
         floatx4 xo[2 * NJT];
 #pragma unroll
         for (int i = 0; i < 2 * NJT; ++i) xo[i] = zero4();
@@ -1045,7 +1046,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
             for (int i = 0; i < 2 * NJT; ++i) {
                 const int t = tb + i / NJT, jt = i % NJT;
                 av[i] = t >= w ? ba[t] : zero4();
-                bv[i] = ldv(s_O + (16 * jt + li) * LDC + 16 * t + 4 * lg);
+                bv[i] = ldv(s_O + (16 * jt + li) * LDC + 16 * max(t, w) + 4 * lg);
             }
             mmn(xo, av, bv);
             load_b(m - 1, tb);

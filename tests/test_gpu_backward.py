@@ -173,6 +173,37 @@ def test_backward_tokens_without_observation(r, dtype):
         check(name, host_f64(got[name]), ref[name])
 
 
+@pytest.mark.parametrize("variant", ["diag", "iso"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_backward_not_finite_output_adjoint(value, variant):
+    """A value of dO at token t that is not finite reaches the gradients of the tokens up to t and
+    of the rest of t's 16-token block, and no other: the gradients of the later blocks are those of
+    the call with a finite value there. One such token in each block of a chunk in turn."""
+    from paper_2609_07816_amd import kdn
+    T = 100
+    x = W.draw_inputs(variant, "f32", 1, T, 2, 32, 64, seed=102, random_state=True)
+    dO, dS, dP = adjoints(x, 102)
+    d = to_device(x)
+
+    def grads(adj):
+        g = kdn.backward(x.variant, *[d[n] for n in NAMES], S0=d["S0"], P0=d["P0"], mu=x.mu,
+                         scale=x.scale, dO=adj, dS_T=torch.from_numpy(dS).cuda(),
+                         dP_T=torch.from_numpy(dP).cuda())
+        torch.cuda.synchronize()
+        return g
+
+    ok = dev_tensor(dO, "f32")
+    ref = grads(ok)
+    for t in (3, 20, 37, 50, 70):
+        adj = ok.clone()
+        adj[0, t, 1, 5] = value
+        got = grads(adj)
+        later = slice(t // 16 * 16 + 16, T)
+        for name in GRADS[:6]:
+            assert torch.equal(got[name][:, later], ref[name][:, later]), (name, t)
+            assert torch.equal(got[name][:, :, 0], ref[name][:, :, 0]), (name, t)
+
+
 # ---------------------------------------------------------------------------------------------
 # full-size workloads (the isotropic B4 T2048 and the diagonal B4 T4096 at H16 d128, bf16), the
 # backward run once over the whole batch, checked on sampled (batch row, head) chains: each
