@@ -1132,10 +1132,19 @@ __global__ __launch_bounds__(NTH) void walk_kernel(WalkArgs a)
     // O = scale (Q_bar S + BA X) of the chunk whose X fragments are held, to LDS; transposed (value
     // rows, token columns), so that a lane's four values are adjacent
     auto put_o = [&]() __attribute__((always_inline)) {
+        // at d_k = 16 in bf16 the two products are of different MFMA shapes. One that adds to the
+        // other's result is issued without the wait that this needs (a probe had half its rows
+        // wrong), so each has its own sum
+        constexpr bool MIX = FK::KF != FC::KF;
+        floatx4 bx[NNT];
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt) bx[nt] = MIX ? zero4() : Oacc[nt];
 #pragma unroll
         for (int s = 0; s < NSC; ++s)
 #pragma unroll
-            for (int nt = 0; nt < NNT; ++nt) Oacc[nt] = FC::mma(Oacc[nt], xf[nt][s], af[s]);
+            for (int nt = 0; nt < NNT; ++nt) bx[nt] = FC::mma(bx[nt], xf[nt][s], af[s]);
+#pragma unroll
+        for (int nt = 0; nt < NNT; ++nt) Oacc[nt] = MIX ? Oacc[nt] + bx[nt] : bx[nt];
 #pragma unroll
         for (int nt = 0; nt < NNT; ++nt)
             store4<TI>(Ost + (16 * w + li) * LDO + 16 * nt + 4 * lg, a.scale * Oacc[nt][0],

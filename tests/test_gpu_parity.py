@@ -75,8 +75,8 @@ def test_forward_bf16_ragged(variant, apc):
 @pytest.mark.parametrize("T", [1, 16, 65, 127])
 def test_forward_tile_edges(T, dk, dv, dtype):
     """Chunks of one token, of whole 16-token blocks, one past and one short of a chunk, over heads
-    with fewer state tiles than waves and output tiles of 16 and 32 columns (rows past the end are
-    not stored: the tokens of the other sequence are checked with them)."""
+    with fewer state tiles than waves, in output tiles of 16 columns (rows past the end are not
+    stored: the tokens of the other sequence are checked with them)."""
     x = W.draw_inputs("diag", dtype, 2, T, 3, dk, dv, seed=49, random_state=True)
     compare_forward(x)
 
@@ -87,6 +87,33 @@ def test_forward_value_tile_widths(N, H, dv, dtype):
     """128 walk workgroups of 32 value columns (split into tiles of 16) and the next count above."""
     x = W.draw_inputs("diag", dtype, N, 65, H, 32, dv, seed=50, random_state=True)
     compare_forward(x)
+
+
+def check_wide(x):
+    """compare_forward, with the variances (a float32 chain of the same inputs in either type) held
+    to the float32 bound."""
+    o, S, P = run_gpu_forward(x)
+    ref = run_oracle_forward(x)
+    check("o", o, ref["o"], TOL[x.dtype])
+    check("S_T", S, ref["S_T"], TOL[x.dtype])
+    check("P_T", P, ref["P_T"], TOL["f32"])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dk", [16, 32, 64, 128])
+@pytest.mark.parametrize("dv", [32, 64, 128])
+def test_forward_wide_value_tiles(dv, dk, dtype):
+    """Value tiles of 32 columns, which take more than 128 workgroups of them: every head size, for
+    chunks of one token, of whole 16-token blocks, one past and one short of a chunk, and a packed
+    batch with empty and one-token sequences. At d_k = 16 there are fewer state tiles than waves,
+    at 64 and 128 a wave's tiles share their key rows."""
+    H = 128 // (2 * (dv // 32)) + 1
+    for T in (1, 16, 65, 127):
+        check_wide(W.draw_inputs("diag", dtype, 2, T, H, dk, dv, seed=55, random_state=True))
+    lens = [1, 0, 63, 64, 0, 130, 5]
+    H = 128 // (len(lens) * (dv // 32)) + 1
+    check_wide(W.draw_inputs("diag", dtype, 1, sum(lens), H, dk, dv, seed=56, lengths=lens,
+                             random_state=True))
 
 
 @pytest.mark.parametrize("variant,apc", [("diag", True), ("iso", True), ("iso", False)])
