@@ -433,7 +433,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
                 }
                 pk[j] = make_float2(ph0 * Kf[j].x, ph1 * Kf[j].y);
                 const float z = wave_sum(vact ? fmaf(pk[j].x, Kf[j].x, pk[j].y * Kf[j].y) : 0.f);
-                const float dn = s_r[t] + z, idn = __builtin_amdgcn_rcpf(dn);
+                // (r is 1 past the end, where z holds 0 times variances that may not be finite)
+                const float dn = s_r[t] + (j < Lw ? z : 0.f), idn = __builtin_amdgcn_rcpf(dn);
                 if (lane == 0) rec[R::DEN + t] = dn;
                 pk[j].x *= idn;
                 pk[j].y *= idn;
@@ -447,7 +448,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
                 }
             } else {
                 const float nn = fmaf(ka[j], n0, Wf[j].x * d0);  // b_hat d
-                const float bh = nn / d0, dn = fmaf(bh, kn[j], s_r[t]), beta = bh / dn;
+                const float bh = j < Lw ? nn / d0 : 0.f;
+                const float dn = fmaf(bh, kn[j], s_r[t]), beta = bh / dn;
                 if (lane == 0) {
                     rec[R::PP_I + t] = n0 / d0;
                     rec[R::PH + t] = bh;
@@ -523,7 +525,8 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
             const int row = 4 * lg + rr;
-            lb[row * LDL + li] = row > li ? t[rr] : (row == li ? 1.f : 0.f);
+            // (rows past the end, zeros times kappa, are zeros also where a kappa is not finite)
+            lb[row * LDL + li] = row > li && row < Lw ? t[rr] : (row == li ? 1.f : 0.f);
         }
     }
     wave_lds_fence();

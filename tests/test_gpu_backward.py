@@ -204,6 +204,24 @@ def test_backward_not_finite_output_adjoint(value, variant):
             assert torch.equal(got[name][:, :, 0], ref[name][:, :, 0]), (name, t)
 
 
+@pytest.mark.parametrize("d", [16, 64])
+def test_backward_infinite_noise_at_the_end(d):
+    """An infinite omega in one channel of a sequence's last token, which stands inside its 16-token
+    block: the chunk's positions past the end carry that variance on. dq reads the gains alone, so
+    it stays finite in the other channels."""
+    from paper_2609_07816_amd import kdn
+    x = W.draw_inputs("diag", "f32", 1, 70, 2, d, d, seed=103, random_state=True)
+    dO, dS, dP = adjoints(x, 103)
+    dd = to_device(x)
+    dd["omega"][0, 69, 0, 2] = float("inf")
+    got = kdn.backward(x.variant, *[dd[n] for n in NAMES], S0=dd["S0"], P0=dd["P0"], mu=x.mu,
+                       scale=x.scale, dO=dev_tensor(dO, "f32"), dS_T=torch.from_numpy(dS).cuda(),
+                       dP_T=torch.from_numpy(dP).cuda())
+    torch.cuda.synchronize()
+    fin = np.isfinite(got["dq"].cpu().numpy())
+    assert np.all(np.delete(fin, 2, axis=3)) and np.all(fin[:, :64])
+
+
 # ---------------------------------------------------------------------------------------------
 # full-size workloads (the isotropic B4 T2048 and the diagonal B4 T4096 at H16 d128, bf16), the
 # backward run once over the whole batch, checked on sampled (batch row, head) chains: each
