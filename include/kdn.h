@@ -80,8 +80,10 @@ typedef enum { KDN_F32 = 0, KDN_BF16 = 1 } kdn_dtype_t;
  *   workspace: device scratch of at least kdn_forward_workspace_bytes(...) bytes
  *   (KDN_ERR_WORKSPACE when smaller or NULL). Four kernels run on `stream` in order: chunk
  *   summaries of the variance chain, a log-depth carry scan across chunks (eq.
- *   chunk-gain-carry), a per-chunk prep that writes each chunk's S-independent operands to the
- *   workspace, and the walk that carries S through the chunks.
+ *   chunk-gain-carry; short sequences of one length have their carries composed by the next
+ *   kernel instead, and those of one chunk no summaries), a per-chunk prep that writes each
+ *   chunk's S-independent operands to the workspace, and the walk that carries S through the
+ *   chunks. A packed batch first has its chunk table and walking order made.
  */
 kdn_status_t kdn_forward_diag(const void* q, const void* k, const void* v, const void* alpha,
                               const void* omega, const void* r, const float* S0, const float* P0,

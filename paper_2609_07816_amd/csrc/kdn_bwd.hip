@@ -234,7 +234,7 @@ __device__ __forceinline__ void store_row(rsrc_t r, bool ok, uint32_t i, float x
 // the variance phases (as the forward's prep, in float32). The products M and M^q run through two
 // operand tiles in LDS, K and Q taking turns in the first: 79 KB at DK = 128, so that two
 // workgroups fit a CU (three tiles would leave one). Bound by its 0.9 GB of traffic and by VALU
-// issue: 230 us at B4 T4096 H16 d128 bf16 (4.0 TB/s) against 655 us when the record held kappa,
+// issue: 226 us at B4 T4096 H16 d128 bf16 (4.1 TB/s) against 655 us when the record held kappa,
 // p_hat, p, the log-decays (float64) and three decayed operands, formed by exponentials.
 // ------------------------------------------------------------------------------------------
 template <class TI, int DK_, int VARIANT_, bool APC_>
@@ -704,7 +704,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void b
 // issued and waits for the newest loads instead of the oldest. Each operand is fetched again right
 // after the step that used it, between the MFMAs: issued in one burst before the barrier, the four
 // waves' loads queue for the CU's one memory pipeline while no MFMA runs. At B4 T4096 H16 d128
-// (one workgroup per CU, 64 chunks in series): 206 and 306 us, against 272 and 393 us with bursts
+// (one workgroup per CU, 64 chunks in series): 206 and 304 us, against 272 and 393 us with bursts
 // and a product's dependent steps in sequence, and 589 and 721 us with the operands staged through
 // LDS and L^-1 applied inside the walk (a third product and barrier per chunk).
 // ------------------------------------------------------------------------------------------
@@ -1118,9 +1118,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
 // The log-decay adjoint of an entry is then q dq + k dk - kappa dkappa; its chunk-end part enters
 // through column sums.
 // 79 KB of LDS and 256 registers: two workgroups per CU, so that one's loads, barriers and scalar
-// phases run under the other's MFMAs. B4 T4096 H16 d128: 704 us against 1222 us with LDS slabs of
+// phases run under the other's MFMAs. B4 T4096 H16 d128: 696 us against 1222 us with LDS slabs of
 // the state and exponentials of float64 log-decays; eight waves with every channel staged at once
 // (156 KB, one workgroup per CU) took 1013 us. Its float32 MFMAs take 300 us, its 1.6 GB 340 us.
+// The compiler keeps 65 values per lane in scratch at DK = 128 (264 bytes; isotropic 57 with gates
+// per channel, 23 with one per head; none at smaller DK): phase 1 holds p3, p4, p5 (96 registers)
+// and a step's state tiles (64) at once, phase 2 the inputs of the tiles ahead.
 template <int DK>
 struct GradLds {
     static constexpr int NKT = DK / 16, NJM = 8;  // value tiles of 16 columns at most

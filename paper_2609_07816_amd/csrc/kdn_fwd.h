@@ -933,8 +933,8 @@ void prep_layer_kernel(PrepArgs a)
 // CU's vector memory pipeline, and by the serial chain: S from LDS, X, X through LDS, S, with two
 // barriers per chunk. With L^-1 folded into the record (KA, BA) there is no third product between X
 // and S and the record is 8 KB smaller; no load, store or tile sits in a branch, and operands are
-// fetched between the products that use the previous ones. 132 us against 189 us for 128 chunks alone
-// (1.03 against 1.48 us per chunk: B1 T8191 H16 d128 bf16), 795 against 928 us for 134,000 packed
+// fetched between the products that use the previous ones. 128 us against 189 us for 128 chunks alone
+// (1.00 against 1.48 us per chunk: B1 T8191 H16 d128 bf16), 796 against 928 us for 134,000 packed
 // tokens, 105 against 133 us at B4 T4096.
 // ------------------------------------------------------------------------------------------
 template <class TI, int DK_, int DV_, int BV_>
@@ -1454,10 +1454,13 @@ hipError_t run_t(const FwdCall& fc, hipStream_t st)
     wa.scale = fc.scale;
     wa.bytes_v = (uint32_t)(ntok * DV * sizeof(TI));
     // Value tiles of 32 columns, or of 16 where tiles of 32 would leave half of the 256 CUs idle: a
-    // chunk's products then take a workgroup half the time (float32, B2 T1024 H8 d64, 32 workgroups
-    // of 32: walk 40 -> 24 us); in bf16 the record, which each workgroup fetches whole, sets the pace
-    // of either (B1 T8191 H16 d128, 64 workgroups of 32: 132 us both). With every CU taken, twice
-    // the workgroups would fetch twice the records.
+    // chunk's products then take a workgroup half the time; in bf16 the record, which each workgroup
+    // fetches whole, sets the pace of either. With every CU taken, twice the workgroups would fetch
+    // twice the records. Whole forwards with tiles of 16 against 32, T2048, for 8, 64, 96 and 128
+    // workgroups of 32: bf16 d128 45.0/47.6, 52.3/53.8, 52.4/53.7, 87.6/88.1 us; float32 d64
+    // 70/103, 107/138, 136/164, 167/187 us (d16 to d128 alike; bf16 d64 at 96 is even). Past it,
+    // T1024, for 192, 256 and 512: bf16 d128 71.8/61.2, 86.2/74.8, 162.6/140.8 us; float32 d64
+    // 132/128, 163/153, 315/292 us.
     if constexpr (DV >= 32) {
         if ((size_t)sa.N * sa.H * (DV / 32) > 128)
             return launch_walk<TI, WalkCfg<TI, DK, DV, 32>>(wa, st);
