@@ -1120,8 +1120,9 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
 // 79 KB of LDS and 256 registers: two workgroups per CU, so that one's loads, barriers and scalar
 // phases run under the other's MFMAs. B4 T4096 H16 d128: 696 us against 1222 us with LDS slabs of
 // the state and exponentials of float64 log-decays; eight waves with every channel staged at once
-// (156 KB, one workgroup per CU) took 1013 us. Its float32 MFMAs take 300 us, its 1.6 GB 340 us.
-// The compiler keeps 65 values per lane in scratch at DK = 128 (264 bytes; isotropic 57 with gates
+// (156 KB, one workgroup per CU) took 1013 us. Its float32 MFMAs take 300 us (41% of the matrix
+// cores' cycles); it moves 2.9 GB past the L2, which a copy does in 600 us. The compiler keeps 65
+// values per lane in scratch at DK = 128 (264 bytes, 0.28 GB of the writes; isotropic 57 with gates
 // per channel, 23 with one per head; none at smaller DK): phase 1 holds p3, p4, p5 (96 registers)
 // and a step's state tiles (64) at once, phase 2 the inputs of the tiles ahead.
 template <int DK>
