@@ -879,8 +879,10 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void b
     }
 }
 
+// (two waves per SIMD: uncapped it takes 258 registers at DK = 128, NJT = 2, and then one workgroup
+// per CU, 18.7 against 16.2 us for one chunk of 128 sequence-heads; capped, one pair goes to scratch)
 template <class TI, int DK, int NJT>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1))) void bw_rwalk(Args a)
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2))) void bw_rwalk(Args a)
 {
     using R = BwRec<DK>;
     using CF = WalkCfg<DK, NJT>;
